@@ -295,3 +295,44 @@ def tolerance(case):
         return {"rel": 2e-6, "max": 1.5e-5}
     # the fp8 matrix instruction adds its products with fewer bits than fp32 holds (1.1e-5 and 1.3e-4)
     return {"rel": 4.5e-5, "max": 5e-4}
+
+
+def _patches(x, win, stride, pad):
+    """One image [c][d][h][w] in 64 bits -> [c * taps][output positions], taps in the order of the weights."""
+    x = torch.nn.functional.pad(x, (pad[2], pad[2], pad[1], pad[1], pad[0], pad[0]))
+    for i, r in enumerate(win):
+        x = x.unfold(1 + i, r, stride)
+    c, o = x.shape[0], x.shape[1:4]
+    return x.permute(0, 4, 5, 6, 1, 2, 3).reshape(c * win[0] * win[1] * win[2], -1), tuple(o)
+
+
+def _conv64(x, w, stride, pad):
+    """x [n][c][d][h][w], w [k][c][t][r][s]: the sums in 64 bits (one image after another, so that the patches stay small)."""
+    w2, out = w.double().reshape(w.shape[0], -1), []
+    for img in x:
+        cols, o = _patches(img.double(), w.shape[2:], stride, pad)
+        out.append((w2 @ cols).reshape((w.shape[0],) + o))
+    return torch.stack(out)
+
+
+def exact(case, seed):
+    """The same inputs, drawn in `prepare`'s order, and plain 64-bit sums; None where the rule after the sums is the result."""
+    c, dtype, g = case, case["dtype"], _gen(seed)
+    if c["kind"] == "matmul":
+        m, n, k, ld = c["m"], c["n"], c["k"], c["k"] + c["pitch"]
+        A, B = _operand(g, dtype, (m, ld), False, 1), _operand(g, dtype, (n, ld), True, k)
+        return A[:, :k].double() @ B[:, :k].double().t()
+    if c["kind"] == "conv" and not c["requant"]:
+        d3, t, r, p = c["d"] > 1, c["t"], c["r"], c["pad"]
+        x = _operand(g, dtype, (c["n"], c["c"], c["d"], c["h"], c["w"]), False, 1)
+        w = _operand(g, dtype, (c["k"], c["c"], t, r, r), True, c["c"] * t * r * r)
+        y = _conv64(x, w, c["stride"], (p if d3 else 0, p, p))
+        return y if d3 else y[:, :, 0]
+    if c["kind"] == "layers":
+        out = []
+        for sh in wl.resnet50_convs():
+            w = _operand(g, dtype, (sh.k, sh.c, sh.r, sh.s), True, sh.c * sh.r * sh.s)
+            x = _operand(g, dtype, (c["batch"], sh.c, sh.h, sh.w), False, 1)
+            out.append(_conv64(x[:, :, None], w[:, :, None], sh.stride, (0, sh.pad, sh.pad))[:, :, 0])
+        return out
+    return None
