@@ -97,6 +97,7 @@ struct IgemmArgs {
     // column range this launch tiles: [col_base, col_limit) of the cols columns (one launch: 0 and cols; a problem
     // whose tile count leaves the last round of workgroups mostly empty is launched as two ranges with two tile shapes)
     int col_base, col_limit;
+    int i8_wide;                                    // out_i8: images are whole numbers of 16-byte pieces
 #ifdef UNIT_PROBE
     // instrumented build only (make probe): per wave 16 x 8 bytes of time stamps, see UNIT_STAMP
     unsigned long long *probe;
@@ -123,10 +124,17 @@ struct IgemmArgs {
 __device__ __forceinline__ int requant_elem(int t, float scale, int relu)
 {
     float g = __fmul_rn((float)t, scale);
-    float i = rintf(g);
-    if (relu) i = fmaxf(i, 0.0f);
-    i = fminf(fmaxf(i, -128.0f), 127.0f);
-    return (int)i;
+    return (int)__builtin_amdgcn_fmed3f(rintf(g), relu ? 0.0f : -128.0f, 127.0f);
+}
+
+// 4 x 4 bytes held by a quad of lanes (lane i: bytes of channels 0..3 at pixel i) transposed (lane i: bytes of pixels
+// 0..3 of channel i): two exchanges inside the quad, one byte selection after each.  All four lanes must be active.
+__device__ __forceinline__ unsigned transpose_quad_bytes(unsigned w, int lane)
+{
+    const unsigned x = (unsigned)__builtin_amdgcn_mov_dpp((int)w, 0xB1, 0xf, 0xf, false);      // quad_perm 1,0,3,2
+    const unsigned t = __builtin_amdgcn_perm(w, x, (lane & 1) ? 0x07030501u : 0x02060004u);
+    const unsigned y = (unsigned)__builtin_amdgcn_mov_dpp((int)t, 0x4E, 0xf, 0xf, false);      // quad_perm 2,3,0,1
+    return __builtin_amdgcn_perm(t, y, (lane & 2) ? 0x07060302u : 0x01000504u);
 }
 
 template <int DT, int MF> struct Mma;
@@ -306,7 +314,13 @@ struct IgemmCfg {
         EDGE_BYTES   = (BSRC == BSRC_NCHWS || BSRC == BSRC_NCHWE) ? 1024 : 0,   // direct reads: first and last 16 bytes of the tensor
         RING_BYTES   = NST * STAGE_BYTES + EDGE_BYTES,
         REDUCE_BYTES = (WGK > 1) ? WGK * BM * BN * 4 : 0,
-        SMEM_BYTES   = (RING_BYTES > REDUCE_BYTES) ? RING_BYTES : REDUCE_BYTES,
+        // int8 NCHW results wait in LDS behind the partial sums (free once the main loop is done); the 32 bytes of
+        // padding spread the eight rows a wave writes at once over all banks.  Not with idle waves (the 16x16 tile).
+        STAGE_I8     = (BM >= 32) ? 1 : 0,
+        I8_BASE      = REDUCE_BYTES,
+        I8_PITCH     = BN + 32,
+        TAIL_BYTES   = REDUCE_BYTES + (STAGE_I8 && DT == DT_I8 ? BM * I8_PITCH : 0),
+        SMEM_BYTES   = (RING_BYTES > TAIL_BYTES) ? RING_BYTES : TAIL_BYTES,
         // direct NCHW reads: a wave-level DMA instruction must cover whole channel rows of the B tile
         ESZ   = (DT == DT_F16 || DT == DT_BF16) ? 2 : 1,
         DIRECT = (BSRC == BSRC_NCHW || BSRC == BSRC_NCHWS || BSRC == BSRC_NCHWE) ? 1 : 0,
@@ -695,32 +709,53 @@ igemm_kernel(const IgemmArgs g)
         }
     };
     // Requantise inputs of one unit (scale, bias, both residual forms), all through buffer descriptors:
-    // absent inputs get an empty range and masked lanes an offset beyond it, both read as zero, so the
-    // loads need no branches and the wave waits once for all of them.
-    auto requant_inputs = [&](int u, float (*sc)[4], unsigned (*add)[4], unsigned *res4) {
-        const __amdgpu_buffer_rsrc_t rsS = make_rsrc(g.scale, UNIT_OOB);
-        const __amdgpu_buffer_rsrc_t rsBi = make_rsrc(g.bias, g.bias ? UNIT_OOB : 0u);
-        const __amdgpu_buffer_rsrc_t rsR = make_rsrc(g.residual, g.residual ? UNIT_OOB : 0u);
-        const __amdgpu_buffer_rsrc_t rsP = make_rsrc(g.res_packed, g.res_packed ? UNIT_OOB : 0u);
+    // an absent bias gets an empty range and masked lanes an offset beyond it, both read as zero.  Scale and bias of a group's four rows
+    // are one 16-byte load each (the range check works per dword, so rows past the last read as zero).
+    auto requant_inputs = [&](int u, float (*sc)[4], unsigned (*add)[4]) {
+        const __amdgpu_buffer_rsrc_t rsS = make_rsrc(g.scale, (unsigned)g.rows * 4u);
+        const __amdgpu_buffer_rsrc_t rsBi = make_rsrc(g.bias, g.bias ? (unsigned)g.rows * 4u : 0u);
 #pragma unroll
         for (int q = 0; q < UG; ++q) {
             int grow, gcol;
             long gcb;
             group_at(u, q, grow, gcol, gcb);
-            const bool col_ok = gcol < col_end;
+            const v4i s4 = buf_load16(rsS, (unsigned)grow * 4u), b4 = buf_load16(rsBi, (unsigned)grow * 4u);
 #pragma unroll
             for (int b = 0; b < 4; ++b) {
-                const int row = grow + b;
-                const unsigned off = row < g.rows ? (unsigned)row * 4u : UNIT_OOB;
-                const unsigned roff = (row < g.rows && col_ok) ? (unsigned)(gcb + (long)row * g.row_stride) * 4u : UNIT_OOB;
-                sc[q][b] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsS, off, 0, 0));
-                add[q][b] = __builtin_amdgcn_raw_buffer_load_b32(rsBi, off, 0, 0) +
-                            __builtin_amdgcn_raw_buffer_load_b32(rsR, roff, 0, 0);
+                const int sb = s4[b];
+                sc[q][b] = __uint_as_float((unsigned)sb);
+                add[q][b] = (unsigned)b4[b];
             }
-            // the four rows of a group are four consecutive output channels of the lane's pixel: the
-            // packed residual arrives as one 32-bit load
-            res4[q] = __builtin_amdgcn_raw_buffer_load_b32(
-                rsP, (grow < g.packed_ld && col_ok) ? (unsigned)((long)gcol * g.packed_ld + grow) : UNIT_OOB, 0, 0);
+        }
+        // (the residuals under scalar branches: their loads, and the multiply per element, are not spent on layers without)
+        if (g.res_packed) {
+            const __amdgpu_buffer_rsrc_t rsP = make_rsrc(g.res_packed, UNIT_OOB);
+#pragma unroll
+            for (int q = 0; q < UG; ++q) {
+                int grow, gcol;
+                long gcb;
+                group_at(u, q, grow, gcol, gcb);
+                // the four rows of a group are four consecutive output channels of the lane's pixel: one 32-bit load
+                const unsigned r4 = __builtin_amdgcn_raw_buffer_load_b32(
+                    rsP, (grow < g.packed_ld && gcol < col_end) ? (unsigned)((long)gcol * g.packed_ld + grow) : UNIT_OOB, 0, 0);
+#pragma unroll
+                for (int b = 0; b < 4; ++b) add[q][b] += (unsigned)((int)(int8_t)(r4 >> (8 * b)) * g.res_mult);
+            }
+        }
+        if (g.residual) {
+            const __amdgpu_buffer_rsrc_t rsR = make_rsrc(g.residual, UNIT_OOB);
+#pragma unroll
+            for (int q = 0; q < UG; ++q) {
+                int grow, gcol;
+                long gcb;
+                group_at(u, q, grow, gcol, gcb);
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const int row = grow + b;
+                    add[q][b] += __builtin_amdgcn_raw_buffer_load_b32(
+                        rsR, (row < g.rows && gcol < col_end) ? (unsigned)(gcb + (long)row * g.row_stride) * 4u : UNIT_OOB, 0, 0);
+                }
+            }
         }
     };
     acc_t acc[TM][TN];
@@ -1144,30 +1179,93 @@ igemm_kernel(const IgemmArgs g)
         } else {
             // every load of the unit is issued before its first store
             float sc[UG][4];
-            unsigned add[UG][4], res4[UG];          // modular sums: the caller bounds only the total
-            requant_inputs(u, sc, add, res4);
+            unsigned add[UG][4];                    // modular sums: the caller bounds only the total
+            requant_inputs(u, sc, add);
+            // What a layer does not ask for is skipped by scalar branches, and no element computes an address of its own:
+            // the epilogue of a short reduction is bound by vector instructions (64 -> 256 channels at 56x56, batch 32:
+            // 213 cycles per wave and element with per-element branches and 64-bit addresses)
+            if (g.store_raw) {
+#pragma unroll
+                for (int q = 0; q < UG; ++q)
+#pragma unroll
+                    for (int b = 0; b < 4; ++b)
+                        if (gcol[q] < col_end && grow[q] + b < g.rows)
+                            out[gcb[q] + (long)(grow[q] + b) * g.row_stride] = val[q][b];
+            }
+            // (rows past the last read a zero scale: their bytes, the padding channels, are zero)
+            unsigned four[UG];
 #pragma unroll
             for (int q = 0; q < UG; ++q) {
-                if (gcol[q] >= col_end) continue;
-                unsigned four = 0;
+                four[q] = 0;
 #pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const int row = grow[q] + b;
-                    if (row >= g.rows) continue;
-                    const long addr = gcb[q] + (long)row * g.row_stride;
-                    const int t = (int)((unsigned)(int)val[q][b] + add[q][b] +
-                                        (unsigned)((int)(int8_t)(res4[q] >> (8 * b)) * g.res_mult));
-                    if (g.store_raw) out[addr] = val[q][b];
-                    const int v = requant_elem(t, sc[q][b], g.relu);
-                    if (g.out_i8) g.out_i8[addr] = (int8_t)v;
-                    four |= ((unsigned)v & 0xffu) << (8 * b);
+                for (int b = 0; b < 4; ++b)
+                    four[q] |= ((unsigned)requant_elem((int)((unsigned)(int)val[q][b] + add[q][b]), sc[q][b], g.relu) & 0xffu) << (8 * b);
+            }
+            if (g.out_i8) {
+#pragma unroll
+                for (int q = 0; q < UG; ++q) {
+                    if (C::STAGE_I8) {
+                        // NCHW bytes: parked in LDS as rows of pixels, a dword of four pixels per lane (stored below)
+                        *reinterpret_cast<unsigned *>(smem + C::I8_BASE + (grow[q] - row0 + (lane & 3)) * C::I8_PITCH +
+                                                      ((gcol[q] - col0) & ~3)) = transpose_quad_bytes(four[q], lane);
+                    } else {
+#pragma unroll
+                        for (int b = 0; b < 4; ++b)
+                            if (gcol[q] < col_end && grow[q] + b < g.rows)
+                                g.out_i8[gcb[q] + (long)(grow[q] + b) * g.row_stride] = (int8_t)(four[q] >> (8 * b));
+                    }
                 }
-                // the int8 results of a group leave as one 32-bit store into the packed (NHWC) output
-                // (padding channels stay zero)
-                if (g.out_packed && grow[q] < g.packed_ld)
-                    *reinterpret_cast<unsigned *>(g.out_packed + (long)gcol[q] * g.packed_ld + grow[q]) = four;
+            }
+            // the int8 results of a group leave as one 32-bit store into the packed (NHWC) output
+            // (padding channels stay zero)
+            if (g.out_packed) {
+#pragma unroll
+                for (int q = 0; q < UG; ++q)
+                    if (gcol[q] < col_end && grow[q] < g.packed_ld)
+                        *reinterpret_cast<unsigned *>(g.out_packed + (long)gcol[q] * g.packed_ld + grow[q]) = four[q];
             }
         }
+    }
+    // int8 NCHW image of the tile, from LDS: a row's pixels leave as 16-byte (images of a whole number of such chunks)
+    // or 4-byte pieces, consecutive lanes one piece after another, so that a wave fills whole 128-byte lines.  (Straight
+    // from the accumulators a lane holds one pixel of four channels: single bytes, in runs of 32.  3x3, 256 channels,
+    // 56x56, batch 32: 109 -> 86 us with the input pass; 1x1, 64 -> 256: 53 -> 33 us.)
+    if (EPI == EPI_REQUANT && C::STAGE_I8 && g.out_i8) {
+        __syncthreads();
+        auto store_rows = [&](auto v_c) {
+            constexpr int V = decltype(v_c)::value, PER_ROW = BN / V;
+            typedef unsigned word_t __attribute__((ext_vector_type(V / 4)));
+            // (a thread stays in its columns and walks down the rows)
+            constexpr int SLOTS = PER_ROW <= 16 ? (PER_ROW <= 8 ? (PER_ROW <= 4 ? (PER_ROW <= 2 ? 2 : 4) : 8) : 16)
+                                                : (PER_ROW <= 32 ? 32 : 64);
+            constexpr int RSTEP = C::NT / SLOTS;
+            const int cc = (tid % SLOTS) * V, r0 = tid / SLOTS, col = col0 + cc;
+            if (cc >= BN || col >= col_end) return;
+            const int n = (g.cols > g.cols_per_img) ? divu(col, g.dv_cpi) : 0;
+            const int pix = col - n * g.cols_per_img;
+            int8_t *dst = g.out_i8 + (long)n * g.img_stride + (long)(row0 + r0) * g.row_stride + pix;
+            const uint8_t *src = smem + C::I8_BASE + r0 * C::I8_PITCH + cc;
+            if (pix + V <= g.cols_per_img && col + V <= col_end) {
+#pragma unroll 4
+                for (int r = r0; r < rows_here; r += RSTEP) {
+                    const word_t w = *reinterpret_cast<const word_t *>(src);
+                    __builtin_memcpy(dst, &w, V);           // (any byte alignment)
+                    src += RSTEP * C::I8_PITCH;
+                    dst += (long)RSTEP * g.row_stride;
+                }
+            } else {
+                // the piece that crosses an image's end (or the last column): byte by byte
+                for (int e = 0; e < V && col + e < col_end; ++e) {
+                    int8_t *d = dst + (long)divu(pix + e, g.dv_cpi) * (g.img_stride - g.cols_per_img) + e;
+                    for (int r = r0; r < rows_here; r += RSTEP) {
+                        *d = (int8_t)src[(r - r0) * C::I8_PITCH + e];
+                        d += (long)RSTEP * g.row_stride;
+                    }
+                }
+            }
+        };
+        if (g.i8_wide) store_rows(IntC<16>{});
+        else           store_rows(IntC<4>{});
     }
 #ifdef UNIT_PROBE
     UNIT_STAMP(4);

@@ -42,7 +42,7 @@ bool tile_fits(int tile, int dtype, int bsrc)
     const int lpt = c.bm / rpi / nw + c.bn / rpi / nw;
     const long edge = (bsrc == BSRC_NCHWS || bsrc == BSRC_NCHW) ? 1024 : 0;   // (NCHW may become NCHWE)
     const long ring = (long)c.nst * (c.bm + c.bn) * c.bkb + edge;
-    const long red = c.wgk > 1 ? (long)c.wgk * c.bm * c.bn * 4 : 0;
+    const long red = (c.wgk > 1 ? (long)c.wgk * c.bm * c.bn * 4 : 0) + (dtype == 0 && c.bm >= 32 ? c.bm * (c.bn + 32) : 0);
     const bool direct = bsrc == BSRC_NCHW || bsrc == BSRC_NCHWS || bsrc == BSRC_NCHWE;
     const int es = (dtype == 1 || dtype == 2) ? 2 : 1;              // fp16 / bf16: two-byte elements
     const int cpr = c.bn * es / 16;                                  // 16-byte chunks per channel row of the B tile

@@ -326,6 +326,7 @@ int conv_packed(const ConvND *d, int dtype, const void *xp, const void *wp,
         a.out_i8 = y_i8;  a.out_packed = static_cast<int8_t *>(y_packed);
         a.packed_ld = pad_channels(d->k, UNIT_I8);
         a.store_raw = y_raw ? 1 : 0;
+        a.i8_wide = (y_i8 && a.PQ % 16 == 0) ? 1 : 0;
     } else {
         a.epi = EPI_RAW;  a.store_raw = 1;  a.bias = fix;
     }
