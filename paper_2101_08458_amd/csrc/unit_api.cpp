@@ -493,14 +493,17 @@ int matmul_any(int dtype, int m, int n, int k, const void *A, long lda, const vo
     const uint8_t *Ap = static_cast<const uint8_t *>(A);
     const uint8_t *Bp = static_cast<const uint8_t *>(B);
     long lda_b = lda * es, ldb_b = ldb * es;
+    PadRows pad[2];
+    int npad = 0;
     if (g.pad_a) {
-        UNIT_HIP(launch_pad_rows(A, lda_b, m, k * es, wsp, g.kpad_bytes, st));
+        pad[npad++] = {Ap, lda_b, wsp, m};
         Ap = wsp;  lda_b = g.kpad_bytes;  wsp += g.a_bytes;
     }
     if (g.pad_b) {
-        UNIT_HIP(launch_pad_rows(B, ldb_b, n, k * es, wsp, g.kpad_bytes, st));
+        pad[npad++] = {Bp, ldb_b, wsp, n};
         Bp = wsp;  ldb_b = g.kpad_bytes;  wsp += g.b_bytes;
     }
+    if (npad) UNIT_HIP(launch_pad_rows(pad, npad, k * es, g.kchunks, st));
     if (g.gemv) {
         UNIT_HIP(launch_gemv(dtype == UNIT_I8 ? DT_I8 : DT_F16, Ap, lda_b, Bp, ldb_b, m, n, g.kchunks, C, ldc, st));
         return UNIT_OK;

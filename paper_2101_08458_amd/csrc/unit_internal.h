@@ -55,8 +55,9 @@ hipError_t launch_pack_act_sub(int dtype, int n, int c, int h, int w, int sh, in
                                const void *x, void *xp, hipStream_t st);
 hipError_t launch_pack_weights(int dtype, int k, int c, int r, int s, const void *w, void *wp, hipStream_t st);
 hipError_t launch_unpack_act_i8(int n, int c, int h, int w, const void *xp, int8_t *x, hipStream_t st);
-hipError_t launch_pad_rows(const void *src, long ld_bytes, int rows, int row_bytes,
-                           void *dst, int dst_row_bytes, hipStream_t st);
+// one operand of launch_pad_rows
+struct PadRows { const uint8_t *src; long ld_bytes; uint8_t *dst; int rows; };
+hipError_t launch_pad_rows(const PadRows *ops, int nops, int row_bytes, int row_chunks, hipStream_t st);
 
 // out[r] = 128 * sum of the signed bytes of row r (rows 16-byte aligned, chunks*16 bytes long)
 hipError_t launch_rowsum128_i8(const void *m, long ld, int rows, int chunks, int32_t *out, hipStream_t st);
