@@ -12,6 +12,8 @@ namespace unit {
 
 #define UNIT_TILE_CASE(ID, BM, BN, BKB, WGM, WGN, WGK, MF, NST, OCC) \
     {BM, BN, BKB, WGM, WGN, WGK, MF, NST},
+#define UNIT_TILE_PLAIN UNIT_TILE_CASE
+#define UNIT_TILE_NONE(ID) {0, 0, 0, 0, 0, 0, 0, 0},
 const TileCfg g_tiles[NUM_TILES] = {
 #include "tiles.def"
 };
@@ -19,6 +21,8 @@ const TileCfg g_tiles_fp8[NUM_TILES] = {
 #include "tiles_fp8.def"
 };
 #undef UNIT_TILE_CASE
+#undef UNIT_TILE_PLAIN
+#undef UNIT_TILE_NONE
 
 // Process-wide override of the rule (unit_debug_force_tile): -1 = none.  Set by tests and tuning
 // sweeps only; the hot path reads two relaxed atomics.
@@ -38,6 +42,7 @@ bool tile_fits(int tile, int dtype, int bsrc)
     if (tile < 0 || tile >= NUM_TILES) return false;
     const TileCfg &c = (dtype == 4 /* fp8 */ ? g_tiles_fp8 : g_tiles)[tile];
     if (c.bm == 0) return false;                                     // no kernel of this tile for the type
+    if (tile == TILE_DEEP && bsrc != BSRC_PLAIN) return false;       // ... nor for conv input (tiles.def)
     const int nw = c.wgm * c.wgn * c.wgk, rpi = 1024 / c.bkb;
     const int lpt = c.bm / rpi / nw + c.bn / rpi / nw;
     const long edge = (bsrc == BSRC_NCHWS || bsrc == BSRC_NCHW) ? 1024 : 0;   // (NCHW may become NCHWE)
@@ -121,6 +126,15 @@ TileChoice select_tile(int rows, int cols, int kchunks, int dtype, int bsrc, boo
                                         (bsrc != BSRC_NCHWS || (cb > 0 && cb % 16 == 0)));
         if (pick && tile_fits(12, dtype, bsrc)) tile = 12;
     }
+    // Plain products of more than one round of 64x64 tiles (two workgroups to a compute unit: 512) and at most one
+    // 128x128 tile per compute unit: nothing else would run beside that tile, so it takes the LDS of four stages.
+    // 1536x1536 and 2048x2048, reduction 2048 (fp16 / int8 / fp8): 24.4 / 13.8 / 13.7 us on 64x64 -> 19.1 / 12.3 / 11.8,
+    // 28.4 / 17.7 / 18.2 us on two stages -> 22.5 / 14.3 / 14.0; a reduction of 128: equal.  With fewer tiles the smaller
+    // shapes win (1024x1024, reduction 4096, fp16: 20 against 29 us), with more the two-stage tile, two of which share a
+    // unit (2176x2048, reduction 1024: 19.7 against 22.7).
+    if (bsrc == BSRC_PLAIN && rows > 16 && (long)cdiv(rows, 64) * cdiv(cols, 64) > 2 * CUS &&
+        (long)cdiv(rows, 128) * cdiv(cols, 128) <= CUS)
+        tile = TILE_DEEP;
     const int forced = g_force_tile.load(std::memory_order_relaxed);
     if (forced >= 0 && forced < NUM_TILES) tile = forced;
 
