@@ -129,11 +129,17 @@ TileChoice select_tile(int rows, int cols, int kchunks, int dtype, int bsrc, boo
     // Plain products of more than one round of 64x64 tiles (two workgroups to a compute unit: 512) and at most one
     // 128x128 tile per compute unit: nothing else would run beside that tile, so it takes the LDS of four stages.
     // 1536x1536 and 2048x2048, reduction 2048 (fp16 / int8 / fp8): 24.4 / 13.8 / 13.7 us on 64x64 -> 19.1 / 12.3 / 11.8,
-    // 28.4 / 17.7 / 18.2 us on two stages -> 22.5 / 14.3 / 14.0; a reduction of 128: equal.  With fewer tiles the smaller
-    // shapes win (1024x1024, reduction 4096, fp16: 20 against 29 us), with more the two-stage tile, two of which share a
-    // unit (2176x2048, reduction 1024: 19.7 against 22.7).
-    if (bsrc == BSRC_PLAIN && rows > 16 && (long)cdiv(rows, 64) * cdiv(cols, 64) > 2 * CUS &&
-        (long)cdiv(rows, 128) * cdiv(cols, 128) <= CUS)
+    // 28.4 / 17.7 / 18.2 us on two stages -> 22.5 / 14.3 / 14.0.  With fewer tiles the smaller shapes win (1024x1024,
+    // reduction 4096, fp16: 20 against 29 us), with more the two-stage tile, two of which share a unit (2176x2048,
+    // reduction 1024: 19.7 against 22.7).
+    // The area counts for nothing here: tiles whose rows are half empty still win against the 64x64 ones (65x20000,
+    // 129x12000 and 130x16384, reductions 64 to 4096: 0.68 to 1.00 of their time in every type; bf16 as fp16; u8i8,
+    // whose A fragments take an XOR per read, 0.81 to 1.05, the high end for reductions of about 1000).
+    // A reduction of one 128-byte step has nothing to stream ahead, and the two-stage tile's shorter prologue is 1 to 3 %
+    // faster there (2048x2048, one step, int8 / fp16 / fp8: 6.65 / 6.66 / 6.69 us against 6.72 / 6.79 / 6.82; two steps: equal;
+    // three: 7.6 against 7.4), so it stays where it was the choice; 64x64 tiles lose also there (1664x1664: 6.7 against 5.7).
+    if (bsrc == BSRC_PLAIN && (long)cdiv(rows, 64) * cdiv(cols, 64) > 2 * CUS &&
+        (long)cdiv(rows, 128) * cdiv(cols, 128) <= CUS && !(tile == 1 && kchunks <= 8))
         tile = TILE_DEEP;
     const int forced = g_force_tile.load(std::memory_order_relaxed);
     if (forced >= 0 && forced < NUM_TILES) tile = forced;
