@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from paper_2101_08458_amd import unit
-from gpu_util import announce, forced
+from gpu_util import announce, chosen_tile, forced
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -52,3 +52,29 @@ def test_matmul_steps_and_edges(dtype):
             fn(m, n, k, a, k, b, k, c, n, ws)
         torch.cuda.synchronize()
         check(c, a, b, dtype)
+
+
+# by the rule, not forced: several bands of eight row tiles with columns that end inside a tile (B of more than 8 MiB: the
+# banded tile order; less: runs along a row tile), row pitch of C beyond its width, tiles with half of their rows empty
+BY_RULE = [(1533, 2001, 4224, 37), (2048, 2048, 272, 0), (129, 12000, 400, 3), (16500, 65, 160, 64), (1100, 1900, 130, 1)]
+
+
+@pytest.mark.parametrize("m,n,k,extra", BY_RULE)
+@pytest.mark.parametrize("dtype", sorted(FNS))
+def test_matmul_chosen_by_the_rule(dtype, m, n, k, extra):
+    ut, fn = FNS[dtype]
+    es = 2 if dtype in ("f16", "bf16") else 1
+    g = torch.Generator(device=DEV)
+    g.manual_seed(4)
+    assert chosen_tile(m, n, -(-k * es // 16), ut) == TILE
+    a, b = operand(g, dtype, (m, k), True), operand(g, dtype, (n, k), False)
+    ldc = n + extra
+    poison = -77 if dtype in ("i8", "u8i8") else float("nan")
+    c = torch.full((m + 1, ldc), poison, device=DEV, dtype=torch.int32 if dtype in ("i8", "u8i8") else torch.float32)
+    ws = torch.empty(max(unit.unit_matmul_workspace(m, n, k, k, k, ut), 256), dtype=torch.uint8, device=DEV)
+    announce("deep ring matmul by the rule", dtype, (m, n, k), "pitch", ldc)
+    fn(m, n, k, a, k, b, k, c, ldc, ws)
+    torch.cuda.synchronize()
+    check(c[:m, :n], a, b, dtype)
+    untouched = torch.cat([c[:m, n:].reshape(-1), c[m]])
+    assert (untouched == -77).all() if dtype in ("i8", "u8i8") else untouched.isnan().all()
