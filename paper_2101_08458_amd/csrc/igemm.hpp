@@ -315,7 +315,9 @@ struct IgemmCfg {
         RING_BYTES   = NST * STAGE_BYTES + EDGE_BYTES,
         REDUCE_BYTES = (WGK > 1) ? WGK * BM * BN * 4 : 0,
         // int8 NCHW results wait in LDS behind the partial sums (free once the main loop is done); the 32 bytes of
-        // padding spread the eight rows a wave writes at once over all banks.  Not with idle waves (the 16x16 tile).
+        // padding spread the eight rows a wave writes at once over all banks (tiles of 32 columns: over half of them, two
+        // rows to a bank).  Not on the 16-row tiles: the 16x16 one has idle waves, and for the 16x64 one (at most 16
+        // channels) it was not tried.
         STAGE_I8     = (BM >= 32) ? 1 : 0,
         I8_BASE      = REDUCE_BYTES,
         I8_PITCH     = BN + 32,
@@ -709,8 +711,9 @@ igemm_kernel(const IgemmArgs g)
         }
     };
     // Requantise inputs of one unit (scale, bias, both residual forms), all through buffer descriptors:
-    // an absent bias gets an empty range and masked lanes an offset beyond it, both read as zero.  Scale and bias of a group's four rows
-    // are one 16-byte load each (the range check works per dword, so rows past the last read as zero).
+    // an absent bias gets an empty range and masked lanes an offset beyond it, both read as zero.  Scale and bias of a
+    // group's four rows are one 16-byte load each (the range check works per dword, so rows past the last read as zero;
+    // the vectors need 4-byte alignment only).
     auto requant_inputs = [&](int u, float (*sc)[4], unsigned (*add)[4]) {
         const __amdgpu_buffer_rsrc_t rsS = make_rsrc(g.scale, (unsigned)g.rows * 4u);
         const __amdgpu_buffer_rsrc_t rsBi = make_rsrc(g.bias, g.bias ? (unsigned)g.rows * 4u : 0u);
@@ -1182,8 +1185,10 @@ igemm_kernel(const IgemmArgs g)
             unsigned add[UG][4];                    // modular sums: the caller bounds only the total
             requant_inputs(u, sc, add);
             // What a layer does not ask for is skipped by scalar branches, and no element computes an address of its own:
-            // the epilogue of a short reduction is bound by vector instructions (64 -> 256 channels at 56x56, batch 32:
-            // 213 cycles per wave and element with per-element branches and 64-bit addresses)
+            // the epilogue of a short reduction is bound by vector instructions.  (Against branches and
+            // 64-bit addresses per element, with the wider scale and bias loads, packed output, kernel times at batch 8: the
+            // 147-tap first layer of a network on the 64x256 tile 22.8 -> 17.2 us, 28x28 layers on 64x64 tiles 7.9 -> 7.0,
+            // 7x7 layers on 16x16 tiles 9.6 -> 9.3.)
             if (g.store_raw) {
 #pragma unroll
                 for (int q = 0; q < UG; ++q)
@@ -1227,9 +1232,10 @@ igemm_kernel(const IgemmArgs g)
         }
     }
     // int8 NCHW image of the tile, from LDS: a row's pixels leave as 16-byte (images of a whole number of such chunks)
-    // or 4-byte pieces, consecutive lanes one piece after another, so that a wave fills whole 128-byte lines.  (Straight
-    // from the accumulators a lane holds one pixel of four channels: single bytes, in runs of 32.  3x3, 256 channels,
-    // 56x56, batch 32: 109 -> 86 us with the input pass; 1x1, 64 -> 256: 53 -> 33 us.)
+    // or 4-byte pieces, consecutive lanes one piece after another, so that a wave writes a tile's row as one run: whole
+    // 128-byte lines where the tile has 128 columns or more.  (Straight from the accumulators a lane holds one pixel of
+    // four channels: single bytes, in runs of 32.  Kernel times at 56x56, batch 32, with the change above: 3x3, 256
+    // channels, 62.4 + 45.0 -> 48.9 + 35.8 us; 1x1, 64 -> 256, 52.3 -> 26.4 us; 1x1, 64 -> 64, 29.1 -> 15.9 us.)
     if (EPI == EPI_REQUANT && C::STAGE_I8 && g.out_i8) {
         __syncthreads();
         auto store_rows = [&](auto v_c) {

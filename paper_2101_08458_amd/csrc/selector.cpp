@@ -133,8 +133,9 @@ TileChoice select_tile(int rows, int cols, int kchunks, int dtype, int bsrc, boo
     // reduction 4096, fp16: 20 against 29 us), with more the two-stage tile, two of which share a unit (2176x2048,
     // reduction 1024: 19.7 against 22.7).
     // The area counts for nothing here: tiles whose rows are half empty still win against the 64x64 ones (65x20000,
-    // 129x12000 and 130x16384, reductions 64 to 4096: 0.68 to 1.00 of their time in every type; bf16 as fp16; u8i8,
-    // whose A fragments take an XOR per read, 0.81 to 1.05, the high end for reductions of about 1000).
+    // 129x12000 and 130x16384, reductions 64 to 4096: 0.77 to 1.00 of their time in every type).  bf16 gains what fp16 does;
+    // u8i8, whose A fragments take an XOR per read, gains less (0.80 to 1.05 of the 64x64 tile's time, the high end on
+    // some shapes for reductions of about 1000 and below 1 again on either side).
     // A reduction of one 128-byte step has nothing to stream ahead, and the two-stage tile's shorter prologue is 1 to 3 %
     // faster there (2048x2048, one step, int8 / fp16 / fp8: 6.65 / 6.66 / 6.69 us against 6.72 / 6.79 / 6.82; two steps: equal;
     // three: 7.6 against 7.4), so it stays where it was the choice; 64x64 tiles lose also there (1664x1664: 6.7 against 5.7).
