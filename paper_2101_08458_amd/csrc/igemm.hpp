@@ -51,7 +51,9 @@ enum { EPI_RAW = 0, EPI_REQUANT = 1 };
 // BSRC_GATHERU is the gather for layers whose pixels hold a whole number of steps of channel chunks: every lane
 // of a step then works on the same tap and the tap walk is scalar (the launcher picks it; callers say BSRC_GATHER).
 // BSRC_NCHWE is the 1x1 direct read for rows that are not dword-aligned (IgemmArgs::edge; picked by the launcher).
-enum { BSRC_PLAIN = 0, BSRC_GATHER = 1, BSRC_NCHW = 2, BSRC_NCHWS = 3, BSRC_GATHERU = 4, BSRC_NCHWE = 5 };
+// BSRC_GATHERW is the gather for windows of more than 31 tap rows (over all planes) or tap columns, which the bit
+// masks of the other two gathers cannot hold (picked by the launcher).
+enum { BSRC_PLAIN = 0, BSRC_GATHER = 1, BSRC_NCHW = 2, BSRC_NCHWS = 3, BSRC_GATHERU = 4, BSRC_NCHWE = 5, BSRC_GATHERW = 6 };
 
 // Divisor with its reciprocal for the kernels' integer divisions: m = floor(2^32 / d) (0xffffffff for d = 1).
 // The host fills these in; a division is then a multiply-high and one correction (see divu).
@@ -98,6 +100,7 @@ struct IgemmArgs {
     // whose tile count leaves the last round of workgroups mostly empty is launched as two ranges with two tile shapes)
     int col_base, col_limit;
     int i8_wide;                                    // out_i8: images are whole numbers of 16-byte pieces
+    unsigned tap_planes;                            // bit t * R for every tap plane t (masked gathers, T > 1)
 #ifdef UNIT_PROBE
     // instrumented build only (make probe): per wave 16 x 8 bytes of time stamps, see UNIT_STAMP
     unsigned long long *probe;
@@ -265,6 +268,13 @@ __device__ __forceinline__ v4i buf_load16(__amdgpu_buffer_rsrc_t r, unsigned off
 __device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t r, uint8_t *lds, unsigned off)
 {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)lds, 16, off, 0, 0, 0);
+}
+// The same with a wave-uniform byte offset on top, which costs no vector instruction.  Lanes that must read zeros carry
+// an `off` that is out of range by itself and every other lane's off + soff lies inside the buffer, with soff never beyond
+// the buffer's length: the result does not depend on whether the range check looks at off or at the sum.
+__device__ __forceinline__ void dma16s(__amdgpu_buffer_rsrc_t r, uint8_t *lds, unsigned off, unsigned soff)
+{
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)lds, 16, off, soff, 0, 0);
 }
 // Transposing LDS reads (ds_read_b64_tr_b8 / _b16) as inline assembly.  Through the compiler's builtins every such
 // read is preceded by s_waitcnt vmcnt(0): the compiler cannot tell which LDS bytes the global -> LDS loads in flight
@@ -445,8 +455,12 @@ igemm_kernel(const IgemmArgs g)
     const __amdgpu_buffer_rsrc_t rsB = (BSRC != BSRC_PLAIN)
         ? make_rsrc(g.B, (unsigned)g.b_bytes)
         : make_rsrc(g.B + (long)col0 * g.ldb, (unsigned)((long)(cols_here - 1) * g.ldb + (long)g.kchunks * 16));
+    constexpr bool MASKED = (BSRC == BSRC_GATHER || BSRC == BSRC_GATHERU);      // gathers with tap masks
+    constexpr bool GATHERS = MASKED || BSRC == BSRC_GATHERW;
     unsigned offB[IB];
     int bd0[IB], bh0[IB], bw0[IB];
+    // masked gathers: bit i set = tap row i (over all planes) / tap column i of this column lies outside the image
+    unsigned no_row[IB], no_col[IB];
 #pragma unroll
     for (int j = 0; j < IB; ++j) {
         int r = (j * NW + wave) * RPI + lr_blk;
@@ -473,7 +487,7 @@ igemm_kernel(const IgemmArgs g)
             offB[j] = (unsigned)(((img * g.Cin + crow) * g.PQ + (px - img * g.PQ)) * ES);
             bh0[j] = crow;                          // channel row of this lane inside a step
             bd0[j] = bw0[j] = 0;
-        } else if (BSRC == BSRC_GATHER || BSRC == BSRC_GATHERU) {
+        } else if (GATHERS) {
             int cc = valid ? col0 + r : 0;
             // (integer divisions are ~40 instructions each: skip the ones whose result is known)
             int n = 0, opq = cc;
@@ -481,11 +495,38 @@ igemm_kernel(const IgemmArgs g)
             int o = 0, pq = opq;
             if (g.PQ > g.P * g.Q) { o = divu(opq, g.dv_ppq); pq = opq - o * (g.P * g.Q); }   // output depth > 1
             int p = divu(pq, g.dv_q), q = pq - p * g.Q;
-            // an invalid column gets a row far outside the image: its bounds test always fails
             const int bd = o * g.sd - g.pd, bh = p * g.sh - g.ph, bw = q * g.sw - g.pw;
-            bd0[j] = bd;
-            bh0[j] = valid ? bh : -0x100000;
-            bw0[j] = bw;
+            if (MASKED) {
+                // Which taps fall outside the image is worked out once, as bit masks: the step loop then spends four vector
+                // instructions on a load where three bounds tests took eleven, most of them a round trip through scalar
+                // registers.  (3x3, fp16, batch 16, repeated on warm caches, with the loads' uniform offsets below: 256
+                // channels at 14x14 11.0 -> 9.9 us, 512 at 7x7 17.3 -> 15.2.  Without padding every tap of a valid column
+                // is inside.)
+                no_row[j] = no_col[j] = 0;
+                if ((g.ph | g.pw | g.pd) != 0) {
+                    auto bits = [](int base, int size, int taps) {      // taps [lo, hi) read positions 0 .. size - 1
+                        const int lo = base < 0 ? (-base < taps ? -base : taps) : 0;
+                        const int left = size - base;
+                        const int hi = left < taps ? (left < 0 ? 0 : left) : taps;
+                        return ((1u << hi) - 1u) & ~((1u << lo) - 1u);
+                    };
+                    unsigned rows = bits(bh, g.H, g.R);
+                    if (g.T > 1 || g.D > 1) {
+                        const int lo = bd < 0 ? (-bd < g.T ? -bd : g.T) : 0, left = g.D - bd;
+                        const int hi = left < g.T ? (left < 0 ? 0 : left) : g.T;
+                        rows *= g.tap_planes & ((1u << (hi * g.R)) - 1u) & ~((1u << (lo * g.R)) - 1u);
+                    }
+                    no_row[j] = ~rows;
+                    no_col[j] = ~bits(bw, g.W, g.S);
+                }
+                if (!valid) no_row[j] = ~0u;
+                bd0[j] = bh0[j] = bw0[j] = 0;
+            } else {
+                // an invalid column gets a row far outside the image: its bounds test always fails
+                bd0[j] = bd;
+                bh0[j] = valid ? bh : -0x100000;
+                bw0[j] = bw;
+            }
             // byte offset of tap (0,0,0); modulo 2^32 (negative in the padding), exact once a tap is in range
             offB[j] = (unsigned)(((n * g.D + bd) * g.H + bh) * g.W + bw) * (unsigned)(g.CB * 16);
         } else {
@@ -493,11 +534,15 @@ igemm_kernel(const IgemmArgs g)
             bd0[j] = bh0[j] = bw0[j] = 0;
         }
     }
-    // conv: reduction chunk kc -> (r, s, channel chunk cb), advanced incrementally per step
-    int kc = ks_begin * NCH + cT;
+    // first reduction chunk of the tile issued next, and the byte offset of its step inside the rows of A (and of a plain
+    // B): wave-uniform, added by the loads themselves (dma16s)
+    int kc0 = ks_begin * NCH;
+    unsigned so = (unsigned)kc0 * 16u;
+    // conv: reduction chunk kc0 + cT -> (r, s, channel chunk cb), advanced incrementally per step
     int ct = 0, cr = 0, cs = 0, ccb = 0;
     constexpr bool uni_tap = (BSRC == BSRC_GATHERU);
-    if (BSRC == BSRC_GATHER) {
+    if (BSRC == BSRC_GATHER || BSRC == BSRC_GATHERW) {
+        const int kc = kc0 + cT;
         int trs = divu(kc, g.dv_cb);
         ccb = kc - trs * g.CB;
         int tr = divu(trs, g.dv_s);                 // tap rows from the start (over all planes)
@@ -508,21 +553,27 @@ igemm_kernel(const IgemmArgs g)
 
     // Gather fast path: when the channel chunks of a pixel are a whole number of steps
     // (CB % NCH == 0) every lane of a step works on the same tap, so the tap walk is scalar:
-    // (ut, ur, us) and the byte offset `utap` of (tap, first chunk of the step) inside the packed
-    // tensor.  Consecutive chunks are consecutive in memory across the s axis, so utap only
-    // jumps when a tap row or plane ends.
-    int ut = 0, ur = 0, us = 0, ucb = 0;
+    // tap row `ur` of its plane, tap row `utr` over all planes, tap column `us`, and the byte offset `utap` of (tap, first
+    // chunk of the step) inside the packed tensor.  Consecutive chunks are consecutive in memory across the s axis, so
+    // utap only jumps when a tap row or plane ends.
+    int utr = 0, ur = 0, us = 0, ucb = 0;
     unsigned utap = 0;
     if (uni_tap) {
         if (ks_begin != 0) {                    // only the later slices of a split reduction
             const int chunk0 = ks_begin * NCH;
             const int trs = chunk0 / g.CB;
             ucb = chunk0 - trs * g.CB;
-            ut = trs / (g.R * g.S);
-            const int rs = trs - ut * (g.R * g.S);
-            ur = rs / g.S;
-            us = rs - ur * g.S;
+            utr = trs / g.S;
+            us = trs - utr * g.S;
+            const int ut = utr / g.R;
+            ur = utr - ut * g.R;
             utap = (unsigned)(((ut * g.H + ur) * g.W + us) * g.CB + ucb) * 16u;
+            // (the divisions leave their results in vector registers; the tap walk is scalar work)
+            ucb = __builtin_amdgcn_readfirstlane(ucb);
+            utr = __builtin_amdgcn_readfirstlane(utr);
+            ur = __builtin_amdgcn_readfirstlane(ur);
+            us = __builtin_amdgcn_readfirstlane(us);
+            utap = (unsigned)__builtin_amdgcn_readfirstlane((int)utap);
         }
 #pragma unroll
         for (int j = 0; j < IB; ++j) offB[j] += (unsigned)cT * 16u;   // this lane's chunk inside the step
@@ -545,14 +596,34 @@ igemm_kernel(const IgemmArgs g)
     if (EDGE1) rt_cb = ks_begin * NCH;  // 1x1 mode: first reduction chunk of the step being read
     int it_base = ((it_r - g.ph) * g.W + (it_s - g.pw)) * ES, it_cbo = it_cb * EPC * ES * g.PQ;
 
-    // issues the DMA of the next tile (the one whose chunk for this thread is kc) into `stage`
-    auto issue_tile = [&](int stage) {
-        const bool kok = kc < kend;
-        const unsigned kbyte = (unsigned)(kc - cT) * 16u;          // = step * BKB
-        uint8_t *dst = smem + stage * C::STAGE_BYTES + wave * 1024;
+    // Before the last tile of the slice, and every tile past it, is issued: the step's uniform offset moves into the lanes'
+    // own, and lanes whose chunk lies past the slice's end get one out of range (they read zeros; past the last tile those
+    // are all lanes).  A scalar branch taken a few times per workgroup; all other tiles cost no masking (8192^3 fp16 958 ->
+    // 932 us, 32x4096x4096 bf16 9.2 -> 8.9).  Not in the direct
+    // modes, whose small tiles have one or two loads a step to mask and wait for instructions at their cold start: there
+    // the branch's code at every copy of the step cost the 53 batch-1 layers 1.3 %.
+    constexpr bool FOLD = !(NCHW1 || BSRC == BSRC_NCHWS);
+    auto issue_begin = [&]() {
+        if (!FOLD || kc0 + NCH < kend) return;
+        const bool kok = kc0 + cT < kend;
 #pragma unroll
-        for (int j = 0; j < IA; ++j)
-            dma16(rsA, dst + j * NW * 1024, kok ? offA[j] + kbyte : UNIT_OOB);
+        for (int j = 0; j < IA; ++j) offA[j] = kok ? offA[j] + so : UNIT_OOB;
+#pragma unroll
+        for (int j = 0; j < IB; ++j) {
+            if (BSRC == BSRC_PLAIN) offB[j] = kok ? offB[j] + so : UNIT_OOB;
+            if (MASKED) no_row[j] = kok ? no_row[j] : ~0u;
+        }
+        so = 0;
+    };
+    // issues the DMA of the next tile (the one whose first chunk is kc0) into `stage`
+    auto issue_tile = [&](int stage) {
+        uint8_t *dst = smem + stage * C::STAGE_BYTES + wave * 1024;
+        const bool kok = kc0 + cT < kend;
+#pragma unroll
+        for (int j = 0; j < IA; ++j) {
+            if (FOLD) dma16s(rsA, dst + j * NW * 1024, offA[j], so);
+            else      dma16(rsA, dst + j * NW * 1024, kok ? offA[j] + (unsigned)kc0 * 16u : UNIT_OOB);
+        }
         dst += BM * BKB;
         if (BSRC == BSRC_NCHWS) {
             // first byte this step needs of channel row 0 of its block: pixel col0 + delta of channel
@@ -561,7 +632,7 @@ igemm_kernel(const IgemmArgs g)
             // as zeros: the few real pixels it holds (first and last channel only) are patched at the read
             // (it_base: byte offset of the tap, recomputed when the tap changes; it_cbo: of the channel block)
             const int base = it_base + it_cbo;
-            const bool step_ok = (kc - cT) < kend;
+            const bool step_ok = kc0 < kend;
 #pragma unroll
             for (int j = 0; j < IB; ++j) {
                 const int off = base + bd0[j];
@@ -579,7 +650,7 @@ igemm_kernel(const IgemmArgs g)
         } else if (NCHW1) {
             // channel rows of this step: chan0 .. chan0 + BKB/ES; rows past the real channel
             // count or past the slice end come back as zeros
-            const int chan0 = (kc - cT) * EPC;
+            const int chan0 = kc0 * EPC;
             const int chan_end = (kend * EPC < g.Cin) ? kend * EPC : g.Cin;
             // (edge variant: a chunk that is not wholly inside the tensor is not loaded: see read_frags)
             const unsigned lim = EDGE1 ? (unsigned)g.b_bytes : 0xffffffffu;
@@ -590,13 +661,11 @@ igemm_kernel(const IgemmArgs g)
                 dma16(rsB, dst + j * NW * 1024, ok ? off : UNIT_OOB);
             }
         } else if (BSRC == BSRC_GATHERU) {
-            const bool step_ok = (kc - cT) < kend;
+            // (an offset whose tap is outside the image gets its top bit set, i.e. is out of range)
 #pragma unroll
             for (int j = 0; j < IB; ++j) {
-                const int dd = bd0[j] + ut, h = bh0[j] + ur, w = bw0[j] + us;
-                const bool ok = step_ok & ((unsigned)dd < (unsigned)g.D) & ((unsigned)h < (unsigned)g.H) &
-                                ((unsigned)w < (unsigned)g.W);
-                dma16(rsB, dst + j * NW * 1024, ok ? offB[j] + utap : UNIT_OOB);
+                const unsigned out = (no_row[j] << ((31 - utr) & 31)) | (no_col[j] << ((31 - us) & 31));
+                dma16(rsB, dst + j * NW * 1024, (out & UNIT_OOB) | (offB[j] + utap));
             }
             ucb += NCH;
             utap += NCH * 16u;
@@ -604,22 +673,31 @@ igemm_kernel(const IgemmArgs g)
                 ucb = 0;
                 if (++us == g.S) {
                     us = 0;
+                    ++utr;
                     utap += (unsigned)((g.W - g.S) * g.CB) * 16u;
                     if (++ur == g.R) {
                         ur = 0;
-                        ++ut;
                         utap += (unsigned)((g.H - g.R) * g.W * g.CB) * 16u;
                     }
                 }
             }
-        } else if (BSRC == BSRC_GATHER) {
+        } else if (BSRC == BSRC_GATHER || BSRC == BSRC_GATHERW) {
             const unsigned tap = (unsigned)(((ct * g.H + cr) * g.W + cs) * g.CB + ccb) * 16u;
+            if (MASKED) {
+                const int trow = ct * g.R + cr;
 #pragma unroll
-            for (int j = 0; j < IB; ++j) {
-                const int dd = bd0[j] + ct, h = bh0[j] + cr, w = bw0[j] + cs;
-                const bool ok = kok & ((unsigned)dd < (unsigned)g.D) & ((unsigned)h < (unsigned)g.H) &
-                                ((unsigned)w < (unsigned)g.W);
-                dma16(rsB, dst + j * NW * 1024, ok ? offB[j] + tap : UNIT_OOB);
+                for (int j = 0; j < IB; ++j) {
+                    const unsigned out = (no_row[j] << ((31 - trow) & 31)) | (no_col[j] << ((31 - cs) & 31));
+                    dma16(rsB, dst + j * NW * 1024, (out & UNIT_OOB) | (offB[j] + tap));
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < IB; ++j) {
+                    const int dd = bd0[j] + ct, h = bh0[j] + cr, w = bw0[j] + cs;
+                    const bool ok = kok & ((unsigned)dd < (unsigned)g.D) & ((unsigned)h < (unsigned)g.H) &
+                                    ((unsigned)w < (unsigned)g.W);
+                    dma16(rsB, dst + j * NW * 1024, ok ? offB[j] + tap : UNIT_OOB);
+                }
             }
             // whole taps to move on by (several when a pixel holds fewer chunks than a step), then whole tap rows
             // and planes: three divisions by reciprocal multiplies, no branches (per-lane loops here cost the
@@ -636,10 +714,10 @@ igemm_kernel(const IgemmArgs g)
             ct += qr;
         } else {
 #pragma unroll
-            for (int j = 0; j < IB; ++j)
-                dma16(rsB, dst + j * NW * 1024, kok ? offB[j] + kbyte : UNIT_OOB);
+            for (int j = 0; j < IB; ++j) dma16s(rsB, dst + j * NW * 1024, offB[j], so);
         }
-        kc += NCH;
+        so += NCH * 16u;
+        kc0 += NCH;
     };
 
     // ---- fragment addressing (lane -> row inside an MFMA tile, 16-byte chunk along k)
@@ -943,7 +1021,10 @@ igemm_kernel(const IgemmArgs g)
                   lane == 0 ? 0u : lane == 1 ? (unsigned)(g.b_bytes - 16) : UNIT_OOB);
         UNIT_STAMP(6);
 #pragma unroll
-        for (int t = 0; t < AHEAD; ++t) issue_tile(t);          // (zeros past the slice end)
+        for (int t = 0; t < AHEAD; ++t) {                       // (zeros past the slice end)
+            issue_begin();
+            issue_tile(t);
+        }
         UNIT_STAMP(7);
         UNIT_WAIT_VM_LGKM0((AHEAD - 1) * C::LPT);               // own part of tile 0 has landed
         UNIT_BARRIER();
@@ -961,6 +1042,7 @@ igemm_kernel(const IgemmArgs g)
                 constexpr int STG = decltype(stage_c)::value;
                 constexpr int next_stage = (STG + 1) % NST;
                 constexpr int prev_stage = (STG + NST - 1) % NST;
+                issue_begin();
 #ifdef UNIT_PROBE
                 const unsigned unit_c0 = UNIT_CYC();
 #endif
@@ -1022,6 +1104,7 @@ igemm_kernel(const IgemmArgs g)
         read_frags(0, 0, 0);
         for (int ks = ks_begin; ks < ks_end; ++ks) {
             const int next_stage = (stage + 1 == NST) ? 0 : stage + 1;
+            issue_begin();
 #pragma unroll
             for (int s2 = 0; s2 < NS; ++s2) {
                 const int slot = s2 & 1;

@@ -317,6 +317,7 @@ int conv_packed(const ConvND *d, int dtype, const void *xp, const void *wp,
     a.per_img = (nchw_direct && d->n > 1 && ((long)d->d * d->h * d->w) % chunk_elems(dtype) != 0) ? 1 : 0;
     a.T = d->t;  a.R = d->r;  a.S = d->s;
     a.sd = d->stride_d;  a.sh = d->stride_h;  a.sw = d->stride_w;  a.pd = d->pad_d;  a.ph = d->pad_h;  a.pw = d->pad_w;
+    for (int t = 0; t < d->t && (long)t * d->r < 31; ++t) a.tap_planes |= 1u << (t * d->r);
     a.out = y_raw;  a.row_stride = a.PQ;  a.img_stride = (long)d->k * a.PQ;  a.cols_per_img = a.PQ;
     if (rq) {
         a.epi = EPI_REQUANT;  a.scale = rq->scale;  a.bias = rq->bias;  a.residual = rq->residual;

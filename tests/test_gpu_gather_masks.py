@@ -1,0 +1,36 @@
+"""Gather of packed activations: the tap masks at their limits (31 tap rows over all planes, 31 tap columns; wider windows take the
+kernel with a bounds test per tap), padding wider than the window, unpadded windows, planes in the padding.  Pixels of whole steps of
+channels (scalar tap walk) and of less (a tap per lane).  Integer sums, bit-exact."""
+import pytest
+import torch
+
+import oracle
+from paper_2101_08458_amd import unit, workloads as wl
+from gpu_util import announce, dev, forced, host, same
+
+pytestmark = pytest.mark.gpu
+
+# (d, h, w), (t, r, s), stride, pad
+CASES = [((1, 33, 6), (1, 31, 2), (1, 1, 1), (0, 15, 1)), ((1, 34, 5), (1, 32, 1), (1, 1, 1), (0, 16, 0)),
+         ((1, 4, 35), (1, 2, 31), (1, 1, 2), (0, 1, 15)), ((1, 3, 34), (1, 1, 32), (1, 1, 1), (0, 0, 16)),
+         ((33, 3, 3), (31, 1, 2), (1, 1, 1), (15, 0, 1)), ((7, 9, 8), (5, 6, 3), (1, 2, 1), (2, 3, 1)),
+         ((6, 9, 8), (4, 8, 3), (2, 1, 1), (1, 4, 1)), ((1, 5, 4), (1, 3, 3), (1, 2, 1), (0, 5, 4)),
+         ((2, 5, 4), (1, 3, 1), (1, 1, 1), (3, 1, 0)), ((3, 8, 7), (2, 3, 3), (1, 2, 1), (0, 0, 0))]
+
+
+@pytest.mark.parametrize("dims,win,stride,pad", CASES)
+@pytest.mark.parametrize("c", [128, 24])
+def test_taps_at_the_border(c, dims, win, stride, pad):
+    g = wl.rng(130, c + sum(dims))
+    x, w = wl.int8_activations(g, (2, c) + dims), wl.int8_weights(g, (20, c) + win)
+    ref = oracle.conv3d_i8(x, w, stride, pad)
+    d = unit.conv3d_desc(2, c, *dims, 20, *win, stride, pad)
+    xd, wd = dev(x), dev(w)
+    for tile, split in [(None, None), (3, 2), (4, 1), (1, 1), (8, 1)]:
+        announce("tap masks", c, dims, win, stride, pad, "tile", tile, "split", split)
+        with forced(tile=tile, split=split):
+            ws = torch.empty(max(unit.unit_conv3d_workspace(d, unit.UNIT_I8), 256), dtype=torch.uint8, device="cuda:0")
+            y = torch.full(ref.shape, -7, dtype=torch.int32, device="cuda:0")
+            unit.unit_conv3d_i8(d, xd, wd, y, ws)
+        torch.cuda.synchronize()
+        assert same(host(y), ref, f"tile {tile} split {split}")
