@@ -9,6 +9,9 @@ unit, written by the Makefile) and fails when a variant that uses the inline-ass
 or spilled vector registers.  Variants that keep the compiler's builtins (32-byte fragments on wave windows of eight or more
 MFMA tiles: igemm.hpp, ASM_TR) may spill and are only listed.
 
+The 256-row tiles of 16x16 accumulators issue their MFMAs as inline assembly, whose operands must not be written by
+vector instructions just before; a spilled register would be copied there, so those kernels must not spill either.
+
 usage: check_resources.py FILE.res [FILE.res ...]      exit status 1 on a violation
 """
 import re
@@ -34,10 +37,12 @@ def kernels(path):
 
 
 def main(paths):
-    bad, seen, spilled_builtin = [], 0, 0
+    bad, quad, seen, spilled_builtin = [], [], 0, 0
     for p in paths:
         for k in list(kernels(p)):
             dt, bm, bn, bkb, wgm, wgn, wgk, mf, nst, occ, bsrc, epi = k["args"]
+            if mf == 16 and bm == 256 and int(k.get("VGPRs Spill", "0")):
+                quad.append((p, k["args"], int(k["VGPRs Spill"])))
             if bsrc not in DIRECT:
                 continue
             fw = 2 if dt == 5 else 1
@@ -56,9 +61,12 @@ def main(paths):
     for p, args, scratch, spills in bad:
         print(f"check_resources: {p}: igemm_kernel<{', '.join(map(str, args))}> uses inline-assembly LDS reads but "
               f"has {scratch} bytes of scratch per lane and {spills} spilled vector registers", file=sys.stderr)
+    for p, args, spills in quad:
+        print(f"check_resources: {p}: igemm_kernel<{', '.join(map(str, args))}> issues its MFMAs as inline assembly but has "
+              f"{spills} spilled vector registers", file=sys.stderr)
     print(f"check_resources: {seen} direct-read variants, {len(bad)} violations, "
           f"{spilled_builtin} builtin-read variants with spills (allowed)")
-    return 1 if bad else 0
+    return 1 if bad or quad else 0
 
 
 if __name__ == "__main__":

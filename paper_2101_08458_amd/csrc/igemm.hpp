@@ -124,6 +124,13 @@ struct IgemmArgs {
 
 // One element of the requantise rule.  v_cvt_f32_i32 and v_rndne_f32 both round to
 // nearest even; the multiply is a single fp32 operation (no fused add exists here).
+// requant_low: the same result in the low byte alone (other bits arbitrary), one instruction less: clamping to integers
+// before rounding gives the same integer, and adding 1.5 * 2^23 rounds to nearest even and leaves it in the low mantissa bits.
+__device__ __forceinline__ unsigned requant_low(int t, float scale, int relu)
+{
+    const float c = __builtin_amdgcn_fmed3f(__fmul_rn((float)t, scale), relu ? 0.0f : -128.0f, 127.0f);
+    return __float_as_uint(__fadd_rn(c, 12582912.0f));
+}
 __device__ __forceinline__ int requant_elem(int t, float scale, int relu)
 {
     float g = __fmul_rn((float)t, scale);
@@ -140,6 +147,10 @@ __device__ __forceinline__ unsigned transpose_quad_bytes(unsigned w, int lane)
     return __builtin_amdgcn_perm(t, y, (lane & 2) ? 0x07060302u : 0x01000504u);
 }
 
+// The 16x16 forms have a second entry, run_acc, with the accumulator pinned to an AGPR tuple: left to itself the compiler keeps
+// part of a 256-register accumulator window in VGPRs and moves it back and forth (404 moves per step of 128 MFMAs).  It does
+// not see the instruction's latency then: the caller keeps other vector writes away from the operands, and calls
+// acc_wait() and acc_done() before anything but another run_acc reads an accumulator.
 template <int DT, int MF> struct Mma;
 template <> struct Mma<DT_I8, 32> {
     typedef v16i acc_t;  typedef int elem_t;  typedef v4i frag_t;  enum { NACC = 16, FW = 1 };
@@ -150,6 +161,8 @@ template <> struct Mma<DT_I8, 16> {
     typedef v4i acc_t;  typedef int elem_t;  typedef v4i frag_t;  enum { NACC = 4, FW = 1 };
     static __device__ __forceinline__ void run(acc_t &c, const v4i &a, const v4i &b)
     { c = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0); }
+    static __device__ __forceinline__ void run_acc(acc_t &c, const v4i &a, const v4i &b)
+    { asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b)); }
 };
 template <> struct Mma<DT_F16, 32> {
     typedef v16f acc_t;  typedef float elem_t;  typedef v4i frag_t;  enum { NACC = 16, FW = 1 };
@@ -160,6 +173,8 @@ template <> struct Mma<DT_F16, 16> {
     typedef v4f acc_t;  typedef float elem_t;  typedef v4i frag_t;  enum { NACC = 4, FW = 1 };
     static __device__ __forceinline__ void run(acc_t &c, const v4i &a, const v4i &b)
     { c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b), c, 0, 0, 0); }
+    static __device__ __forceinline__ void run_acc(acc_t &c, const v4i &a, const v4i &b)
+    { asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b)); }
 };
 
 template <> struct Mma<DT_BF16, 32> {
@@ -171,6 +186,8 @@ template <> struct Mma<DT_BF16, 16> {
     typedef v4f acc_t;  typedef float elem_t;  typedef v4i frag_t;  enum { NACC = 4, FW = 1 };
     static __device__ __forceinline__ void run(acc_t &c, const v4i &a, const v4i &b)
     { c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0); }
+    static __device__ __forceinline__ void run_acc(acc_t &c, const v4i &a, const v4i &b)
+    { asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b)); }
 };
 // fp8: each lane feeds 32 operand bytes; format selectors 0 = E4M3 for both operands, block
 // scales zero = the unscaled form of the instruction
@@ -184,6 +201,18 @@ template <> struct Mma<DT_FP8, 16> {
     static __device__ __forceinline__ void run(acc_t &c, const v8i &a, const v8i &b)
     { c = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 0, 0, 0, 0, 0, 0); }
 };
+// After the last run_acc: 32 wait states (its result needs fewer than 16), and every accumulator passes through a statement
+// behind them, so that nothing reads one earlier.
+__device__ __forceinline__ void acc_wait() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
+template <typename A> __device__ __forceinline__ void acc_done(A &a) { asm volatile("" : "+a"(a)); }
+// One element of an accumulator that run_acc filled.  (A plain read lets the compiler copy all of them to VGPRs ahead of
+// the branches of an epilogue, and spill.)
+template <typename T> __device__ __forceinline__ T acc_read(T x)
+{
+    T v;
+    asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v) : "a"(x));
+    return v;
+}
 template <int MF> struct Mma<DT_U8A, MF> : Mma<DT_I8, MF> {};
 template <int MF> struct Mma<DT_U8B, MF> : Mma<DT_I8, MF> {};
 
@@ -322,7 +351,9 @@ struct IgemmCfg {
         LPT   = IA + IB,
         STAGE_BYTES  = (BM + BN) * BKB,
         EDGE_BYTES   = (BSRC == BSRC_NCHWS || BSRC == BSRC_NCHWE) ? 1024 : 0,   // direct reads: first and last 16 bytes of the tensor
-        RING_BYTES   = NST * STAGE_BYTES + EDGE_BYTES,
+        // 256 rows of 16x16 accumulators on four waves: the loop with pinned accumulators and three buffers of A
+        QUAD  = (MF == 16 && BM == 256 && NW == 4) ? 1 : 0,
+        RING_BYTES   = QUAD ? 3 * BM * BKB + 2 * BN * BKB : NST * STAGE_BYTES + EDGE_BYTES,
         REDUCE_BYTES = (WGK > 1) ? WGK * BM * BN * 4 : 0,
         // int8 NCHW results wait in LDS behind the partial sums (free once the main loop is done); the 32 bytes of
         // padding spread the eight rows a wave writes at once over all banks (tiles of 32 columns: over half of them, two
@@ -615,6 +646,60 @@ igemm_kernel(const IgemmArgs g)
         }
         so = 0;
     };
+    // load j of the B tile of the next tile, and the step to the tile after it (the direct modes have their own, below)
+    auto issue_b = [&](uint8_t *dst, int j) {
+        if (BSRC == BSRC_GATHERU) {
+            // (an offset whose tap is outside the image gets its top bit set, i.e. is out of range)
+            const unsigned out = (no_row[j] << ((31 - utr) & 31)) | (no_col[j] << ((31 - us) & 31));
+            dma16(rsB, dst, (out & UNIT_OOB) | (offB[j] + utap));
+        } else if (BSRC == BSRC_GATHER) {
+            const unsigned tap = (unsigned)(((ct * g.H + cr) * g.W + cs) * g.CB + ccb) * 16u;
+            const unsigned out = (no_row[j] << ((31 - (ct * g.R + cr)) & 31)) | (no_col[j] << ((31 - cs) & 31));
+            dma16(rsB, dst, (out & UNIT_OOB) | (offB[j] + tap));
+        } else if (BSRC == BSRC_GATHERW) {
+            const unsigned tap = (unsigned)(((ct * g.H + cr) * g.W + cs) * g.CB + ccb) * 16u;
+            const int dd = bd0[j] + ct, h = bh0[j] + cr, w = bw0[j] + cs;
+            const bool ok = (kc0 + cT < kend) & ((unsigned)dd < (unsigned)g.D) & ((unsigned)h < (unsigned)g.H) &
+                            ((unsigned)w < (unsigned)g.W);
+            dma16(rsB, dst, ok ? offB[j] + tap : UNIT_OOB);
+        } else {
+            dma16s(rsB, dst, offB[j], so);
+        }
+    };
+    auto issue_next = [&]() {
+        if (BSRC == BSRC_GATHERU) {
+            ucb += NCH;
+            utap += NCH * 16u;
+            if (ucb >= g.CB) {
+                ucb = 0;
+                if (++us == g.S) {
+                    us = 0;
+                    ++utr;
+                    utap += (unsigned)((g.W - g.S) * g.CB) * 16u;
+                    if (++ur == g.R) {
+                        ur = 0;
+                        utap += (unsigned)((g.H - g.R) * g.W * g.CB) * 16u;
+                    }
+                }
+            }
+        } else if (BSRC == BSRC_GATHER || BSRC == BSRC_GATHERW) {
+            // whole taps to move on by (several when a pixel holds fewer chunks than a step), then whole tap rows
+            // and planes: three divisions by reciprocal multiplies, no branches (per-lane loops here cost the
+            // network stems a fifth of their step)
+            ccb += NCH;
+            const int adv = divu(ccb, g.dv_cb);
+            ccb -= adv * g.CB;
+            cs += adv;
+            const int qs = divu(cs, g.dv_s);
+            cs -= qs * g.S;
+            cr += qs;
+            const int qr = divu(cr, g.dv_r);
+            cr -= qr * g.R;
+            ct += qr;
+        }
+        so += NCH * 16u;
+        kc0 += NCH;
+    };
     // issues the DMA of the next tile (the one whose first chunk is kc0) into `stage`
     auto issue_tile = [&](int stage) {
         uint8_t *dst = smem + stage * C::STAGE_BYTES + wave * 1024;
@@ -660,64 +745,11 @@ igemm_kernel(const IgemmArgs g)
                 const bool ok = chan0 + bh0[j] < chan_end && off + 16u <= lim;
                 dma16(rsB, dst + j * NW * 1024, ok ? off : UNIT_OOB);
             }
-        } else if (BSRC == BSRC_GATHERU) {
-            // (an offset whose tap is outside the image gets its top bit set, i.e. is out of range)
-#pragma unroll
-            for (int j = 0; j < IB; ++j) {
-                const unsigned out = (no_row[j] << ((31 - utr) & 31)) | (no_col[j] << ((31 - us) & 31));
-                dma16(rsB, dst + j * NW * 1024, (out & UNIT_OOB) | (offB[j] + utap));
-            }
-            ucb += NCH;
-            utap += NCH * 16u;
-            if (ucb >= g.CB) {
-                ucb = 0;
-                if (++us == g.S) {
-                    us = 0;
-                    ++utr;
-                    utap += (unsigned)((g.W - g.S) * g.CB) * 16u;
-                    if (++ur == g.R) {
-                        ur = 0;
-                        utap += (unsigned)((g.H - g.R) * g.W * g.CB) * 16u;
-                    }
-                }
-            }
-        } else if (BSRC == BSRC_GATHER || BSRC == BSRC_GATHERW) {
-            const unsigned tap = (unsigned)(((ct * g.H + cr) * g.W + cs) * g.CB + ccb) * 16u;
-            if (MASKED) {
-                const int trow = ct * g.R + cr;
-#pragma unroll
-                for (int j = 0; j < IB; ++j) {
-                    const unsigned out = (no_row[j] << ((31 - trow) & 31)) | (no_col[j] << ((31 - cs) & 31));
-                    dma16(rsB, dst + j * NW * 1024, (out & UNIT_OOB) | (offB[j] + tap));
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < IB; ++j) {
-                    const int dd = bd0[j] + ct, h = bh0[j] + cr, w = bw0[j] + cs;
-                    const bool ok = kok & ((unsigned)dd < (unsigned)g.D) & ((unsigned)h < (unsigned)g.H) &
-                                    ((unsigned)w < (unsigned)g.W);
-                    dma16(rsB, dst + j * NW * 1024, ok ? offB[j] + tap : UNIT_OOB);
-                }
-            }
-            // whole taps to move on by (several when a pixel holds fewer chunks than a step), then whole tap rows
-            // and planes: three divisions by reciprocal multiplies, no branches (per-lane loops here cost the
-            // network stems a fifth of their step)
-            ccb += NCH;
-            const int adv = divu(ccb, g.dv_cb);
-            ccb -= adv * g.CB;
-            cs += adv;
-            const int qs = divu(cs, g.dv_s);
-            cs -= qs * g.S;
-            cr += qs;
-            const int qr = divu(cr, g.dv_r);
-            cr -= qr * g.R;
-            ct += qr;
         } else {
 #pragma unroll
-            for (int j = 0; j < IB; ++j) dma16s(rsB, dst + j * NW * 1024, offB[j], so);
+            for (int j = 0; j < IB; ++j) issue_b(dst + j * NW * 1024, j);
         }
-        so += NCH * 16u;
-        kc0 += NCH;
+        issue_next();
     };
 
     // ---- fragment addressing (lane -> row inside an MFMA tile, 16-byte chunk along k)
@@ -862,6 +894,7 @@ igemm_kernel(const IgemmArgs g)
     // The DMA then runs NST-1 tiles ahead and refills the stage read one step EARLIER (whose
     // reads every wave has consumed in its previous step's MFMAs), so the step's barrier needs
     // no wait on outstanding LDS reads: they complete behind the MFMAs and the DMA issue.
+    constexpr bool QUAD = C::QUAD;
     constexpr bool WHOLE = (TM * TN <= 4) && NST >= 3;      // (the register-prefetch schedule needs three LDS stages)
     constexpr int NSLOT = WHOLE ? 2 * NS : 2;
     frag_t fa[NSLOT][TM], fb[NSLOT][TN];
@@ -1016,6 +1049,8 @@ igemm_kernel(const IgemmArgs g)
 
     if (ks_begin < ks_end) {
         constexpr int AHEAD = WHOLE ? NST - 1 : NST;            // tiles in flight after the prologue
+        // QUAD: three buffers of A, then two of B
+        constexpr int A_SZ = BM * BKB, B_SZ = BN * BKB, B_AT = 3 * A_SZ;
         if ((BSRC == BSRC_NCHWS || EDGE1) && wave == 0)   // first and last 16 bytes of the tensor (see read_frags)
             dma16(rsB, smem + NST * C::STAGE_BYTES,
                   lane == 0 ? 0u : lane == 1 ? (unsigned)(g.b_bytes - 16) : UNIT_OOB);
@@ -1023,14 +1058,78 @@ igemm_kernel(const IgemmArgs g)
 #pragma unroll
         for (int t = 0; t < AHEAD; ++t) {                       // (zeros past the slice end)
             issue_begin();
-            issue_tile(t);
+            if constexpr (QUAD) {
+#pragma unroll
+                for (int j = 0; j < IA; ++j) dma16s(rsA, smem + t * A_SZ + wave * 1024 + j * NW * 1024, offA[j], so);
+#pragma unroll
+                for (int j = 0; j < IB; ++j) issue_b(smem + B_AT + t * B_SZ + wave * 1024 + j * NW * 1024, j);
+                issue_next();
+            } else {
+                issue_tile(t);
+            }
         }
         UNIT_STAMP(7);
         UNIT_WAIT_VM_LGKM0((AHEAD - 1) * C::LPT);               // own part of tile 0 has landed
         UNIT_BARRIER();
         UNIT_STAMP(1);
         int stage = 0;
-        if (WHOLE) {
+        if constexpr (QUAD) {
+            // Four waves, one per SIMD, each with a 128-row window of 16x16 accumulators in AGPRs.  Against eight waves of
+            // 128x64 windows a step reads a third less from LDS, and against 32x32 MFMAs the matrix pipes draw less power:
+            // under this load the card's clock is what power leaves (1.4 to 1.8 GHz), so both count (fp16 8192^3: 932 us
+            // on eight waves, 765 here; int8 4096^3 63.6 -> 56.9).  Nothing overlaps a wave's own stalls, so fragment reads and loads are spread
+            // evenly between the MFMAs by hand: the loads of a step, issued in one half of it, stall the wave at the
+            // memory pipe (2930 cycles a step against 2550).  That needs a third buffer of A: its tile two steps ahead
+            // streams in during the first half of a step, B's during the second, when B's buffer is free.
+            static_assert(!QUAD || (C::NKSUB == 2 && WGK == 1 && NST == 2 && FW == 1), "two sub-steps, whole accumulators");
+            static_assert(BSRC == BSRC_PLAIN || MASKED, "B from plain rows or a masked gather");
+            constexpr int NM = TM * TN, NR = TM + TN;
+            constexpr int R_EVERY = (NM * 3 / 4) / NR, A_EVERY = NM / IA, B_EVERY = NM / IB;
+            static_assert(R_EVERY >= 2 && A_EVERY * IA <= NM && B_EVERY * IB <= NM, "every read and load has its place");
+            auto read_one = [&](int at_a, int at_b, int sub, int slot, int x) {
+                const int ch = sub * C::CPL + lchunk;
+                if (x < TN) fb[slot][x] = Frag<FW>::load(smem + at_b + (b_row + x * MF) * BKB, ch, b_swz);
+                else        fa[slot][x - TN] = Frag<FW>::load(smem + at_a + (a_row + (x - TN) * MF) * BKB, ch, a_swz);
+            };
+            int a0 = 0, a1 = A_SZ, a2 = 2 * A_SZ, b0 = B_AT, b1 = B_AT + B_SZ;
+#pragma unroll
+            for (int x = 0; x < NR; ++x) read_one(a0, b0, 0, 0, x);
+            for (int ks = ks_begin; ks < ks_end; ++ks) {
+                issue_begin();
+#pragma unroll
+                for (int half = 0; half < 2; ++half) {
+                    if (half) {
+                        UNIT_WAIT_VM_LGKM0(IA);         // own part of the next tile landed, own reads of this one done
+                        UNIT_BARRIER();
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int r = 0; r < NM; ++r) {
+                        // (back and forth through the columns: an MFMA keeps one operand of the one before it)
+                        const int i = r / TN, j = (i & 1) ? TN - 1 - r % TN : r % TN;
+                        M::run_acc(acc[i][j], fa[half][i], fb[half][j]);
+                        if (r % R_EVERY == R_EVERY - 2 && r / R_EVERY < NR) {
+                            if (!half) read_one(a0, b0, 1, 1, r / R_EVERY);
+                            else       read_one(a1, b1, 0, 0, r / R_EVERY);
+                        }
+                        if (!half && r % A_EVERY == A_EVERY / 2 && r / A_EVERY < IA)
+                            dma16s(rsA, smem + a2 + wave * 1024 + (r / A_EVERY) * NW * 1024, offA[r / A_EVERY], so);
+                        if (half && r % B_EVERY == B_EVERY / 2 && r / B_EVERY < IB)
+                            issue_b(smem + b0 + wave * 1024 + (r / B_EVERY) * NW * 1024, r / B_EVERY);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+                issue_next();
+                const int ta = a0, tb = b0;
+                a0 = a1;  a1 = a2;  a2 = ta;
+                b0 = b1;  b1 = tb;
+            }
+            acc_wait();
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) acc_done(acc[i][j]);
+        } else if (WHOLE) {
 #pragma unroll
             for (int s2 = 0; s2 < NS; ++s2) read_frags(0, s2, s2);
             // The step loop is unrolled over the fragment sets and the stage ring (four steps), so that set and
@@ -1213,6 +1312,118 @@ igemm_kernel(const IgemmArgs g)
         g.bias, !(g.bias && blockIdx.z == 0) ? 0u : (DT == DT_U8B) ? (unsigned)((g.rows * 4 + 255) & ~255) : UNIT_OOB);
     elem_t *out = reinterpret_cast<elem_t *>(g.out);
 
+    if constexpr (QUAD && EPI == EPI_RAW) {
+        // A lane's stores differ by uniform amounts: one offset per column tile in vector registers (out of range for
+        // columns past the end), the row's part added by the store, and a row's columns one after another, which fill whole
+        // lines.  (An address per store, one MFMA tile after another: 12 us for 256 x 256 words at 8192^3; 5.9, and
+        // 6.5 where all 256 workgroups store at once, which is 10 TB/s.)
+        unsigned coff[TN];
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            int r0, col;
+            long at;
+            group_at(j, 0, r0, col, at);
+            coff[j] = col < col_end ? ((unsigned)at + (unsigned)(r0 - row0) * (unsigned)g.row_stride) * 4u : UNIT_OOB;
+        }
+        const int lr0 = wm * C::WTM + acc_row<MF>(0, lane);         // this lane's first row of the tile
+        auto store_window = [&](auto full_c) {
+            constexpr bool FULL = decltype(full_c)::value != 0;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int e = 0; e < NA; ++e) {
+                    const int row = i * MF + e;                     // (16x16 accumulators: element e is row e of four)
+                    const bool in = FULL || lr0 + row < rows_here;
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        __builtin_amdgcn_raw_buffer_store_b32(to_bits(acc[i][j][e]), rsO, in ? coff[j] : UNIT_OOB,
+                                                              (unsigned)row * (unsigned)g.row_stride * 4u, 0);
+                }
+        };
+        if (rows_here == BM) store_window(IntC<1>{});
+        else                 store_window(IntC<0>{});
+    } else if constexpr (QUAD) {
+        // The requantise epilogue below, a row of column tiles at a time: scale and bias of a lane's four rows are fetched once
+        // for all of its columns, and what depends on the column alone is worked out once.  (Per MFMA tile, as below, the
+        // 64 tiles of this window unroll to 16000 instructions with spills: 3x3, 256 channels, 56x56, batch 32, 99.7 us as a
+        // whole, 84.7 here.)
+        const __amdgpu_buffer_rsrc_t rsS = make_rsrc(g.scale, (unsigned)g.rows * 4u);
+        const __amdgpu_buffer_rsrc_t rsBi = make_rsrc(g.bias, g.bias ? (unsigned)g.rows * 4u : 0u);
+        const __amdgpu_buffer_rsrc_t rsP = make_rsrc(g.res_packed, UNIT_OOB);
+        const __amdgpu_buffer_rsrc_t rsR = make_rsrc(g.residual, UNIT_OOB);
+        int gcol[TN];
+        unsigned nchw[TN], pixel[TN];               // element offset of (row 0, column), byte offset of the packed pixel
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            int r0;
+            long at;
+            group_at(j, 0, r0, gcol[j], at);
+            nchw[j] = (unsigned)at;
+            pixel[j] = (unsigned)gcol[j] * (unsigned)g.packed_ld;
+        }
+        const int lr0 = wm * C::WTM + acc_row<MF>(0, lane);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int lr = lr0 + i * MF, grow = row0 + lr;
+            const v4i s4 = buf_load16(rsS, (unsigned)grow * 4u), b4 = buf_load16(rsBi, (unsigned)grow * 4u);
+            v4i add[TN];
+#pragma unroll
+            for (int j = 0; j < TN; ++j) add[j] = b4;
+            if (g.res_packed) {
+                unsigned r4[TN];
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    r4[j] = __builtin_amdgcn_raw_buffer_load_b32(
+                        rsP, (grow < g.packed_ld && gcol[j] < col_end) ? pixel[j] + (unsigned)grow : UNIT_OOB, 0, 0);
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int b = 0; b < 4; ++b)
+                        add[j][b] = (int)((unsigned)add[j][b] + (unsigned)((int)(int8_t)(r4[j] >> (8 * b)) * g.res_mult));
+            }
+            if (g.residual) {
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        add[j][b] = (int)((unsigned)add[j][b] + (unsigned)__builtin_amdgcn_raw_buffer_load_b32(
+                            rsR, (grow + b < g.rows && gcol[j] < col_end)
+                                     ? (nchw[j] + (unsigned)(grow + b) * (unsigned)g.row_stride) * 4u : UNIT_OOB, 0, 0));
+            }
+            if (g.store_raw) {
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        __builtin_amdgcn_raw_buffer_store_b32(to_bits(acc_read(acc[i][j][b])), rsO,
+                            (lr + b < rows_here && gcol[j] < col_end)
+                                ? (nchw[j] + (unsigned)(lr + b) * (unsigned)g.row_stride) * 4u : UNIT_OOB, 0, 0);
+            }
+            unsigned four[TN];
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                unsigned q[4];
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+                    q[b] = requant_low((int)((unsigned)(int)acc_read(acc[i][j][b]) + (unsigned)add[j][b]),
+                                       __uint_as_float((unsigned)s4[b]), g.relu);
+                four[j] = __builtin_amdgcn_perm(q[1], q[0], 0x0c0c0400u) | __builtin_amdgcn_perm(q[3], q[2], 0x04000c0cu);
+            }
+            if (g.out_i8) {
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    *reinterpret_cast<unsigned *>(smem + C::I8_BASE + (lr + (lane & 3)) * C::I8_PITCH +
+                                                  ((gcol[j] - col0) & ~3)) = transpose_quad_bytes(four[j], lane);
+            }
+            if (g.out_packed) {
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    if (gcol[j] < col_end && grow < g.packed_ld)
+                        *reinterpret_cast<unsigned *>(g.out_packed + (long)gcol[j] * g.packed_ld + grow) = four[j];
+            }
+            __builtin_amdgcn_sched_barrier(0);      // (one row at a time: together they do not fit the registers)
+        }
+    } else {
 #pragma clang loop unroll(full)
     for (int u = 0; u < NU; ++u) {
         v4e val[UG];
@@ -1284,10 +1495,11 @@ igemm_kernel(const IgemmArgs g)
             unsigned four[UG];
 #pragma unroll
             for (int q = 0; q < UG; ++q) {
-                four[q] = 0;
+                unsigned r[4];
 #pragma unroll
                 for (int b = 0; b < 4; ++b)
-                    four[q] |= ((unsigned)requant_elem((int)((unsigned)(int)val[q][b] + add[q][b]), sc[q][b], g.relu) & 0xffu) << (8 * b);
+                    r[b] = requant_low((int)((unsigned)(int)val[q][b] + add[q][b]), sc[q][b], g.relu);
+                four[q] = __builtin_amdgcn_perm(r[1], r[0], 0x0c0c0400u) | __builtin_amdgcn_perm(r[3], r[2], 0x04000c0cu);
             }
             if (g.out_i8) {
 #pragma unroll
@@ -1313,6 +1525,7 @@ igemm_kernel(const IgemmArgs g)
                         *reinterpret_cast<unsigned *>(g.out_packed + (long)gcol[q] * g.packed_ld + grow[q]) = four[q];
             }
         }
+    }
     }
     // int8 NCHW image of the tile, from LDS: a row's pixels leave as 16-byte (images of a whole number of such chunks)
     // or 4-byte pieces, consecutive lanes one piece after another, so that a wave writes a tile's row as one run: whole

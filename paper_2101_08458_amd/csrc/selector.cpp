@@ -13,6 +13,7 @@ namespace unit {
 #define UNIT_TILE_CASE(ID, BM, BN, BKB, WGM, WGN, WGK, MF, NST, OCC) \
     {BM, BN, BKB, WGM, WGN, WGK, MF, NST},
 #define UNIT_TILE_PLAIN UNIT_TILE_CASE
+#define UNIT_TILE_QUAD UNIT_TILE_CASE
 #define UNIT_TILE_NONE(ID) {0, 0, 0, 0, 0, 0, 0, 0},
 const TileCfg g_tiles[NUM_TILES] = {
 #include "tiles.def"
@@ -22,6 +23,7 @@ const TileCfg g_tiles_fp8[NUM_TILES] = {
 };
 #undef UNIT_TILE_CASE
 #undef UNIT_TILE_PLAIN
+#undef UNIT_TILE_QUAD
 #undef UNIT_TILE_NONE
 
 // Process-wide override of the rule (unit_debug_force_tile): -1 = none.  Set by tests and tuning
@@ -43,6 +45,7 @@ bool tile_fits(int tile, int dtype, int bsrc)
     const TileCfg &c = (dtype == 4 /* fp8 */ ? g_tiles_fp8 : g_tiles)[tile];
     if (c.bm == 0) return false;                                     // no kernel of this tile for the type
     if (tile == TILE_DEEP && bsrc != BSRC_PLAIN) return false;       // ... nor for conv input (tiles.def)
+    if (tile >= TILE_QUAD && ((bsrc != BSRC_PLAIN && bsrc != BSRC_GATHER) || dtype > 2)) return false;     // (int8, fp16, bf16)
     const int nw = c.wgm * c.wgn * c.wgk, rpi = 1024 / c.bkb;
     const int lpt = c.bm / rpi / nw + c.bn / rpi / nw;
     const long edge = (bsrc == BSRC_NCHWS || bsrc == BSRC_NCHW) ? 1024 : 0;   // (NCHW may become NCHWE)
@@ -142,6 +145,20 @@ TileChoice select_tile(int rows, int cols, int kchunks, int dtype, int bsrc, boo
     if (bsrc == BSRC_PLAIN && (long)cdiv(rows, 64) * cdiv(cols, 64) > 2 * CUS &&
         (long)cdiv(rows, 128) * cdiv(cols, 128) <= CUS && !(tile == 1 && kchunks <= 8))
         tile = TILE_DEEP;
+    // The large tile on four waves, from eight steps on (4096x4096, fp16: 512 bytes of reduction 19.7 us on both, 1024 26.5 ->
+    // 25.5, 2048 38.6 -> 35.8, 8192 117 -> 104; 8192^3 908 -> 765; int8 8192^3 470 -> 400): below, its longer prologue
+    // can cost more than its four steps save (int8 5000x4096x512: 27.0 us against 29.0).
+    if (tile == 8 && kchunks >= 64 && tile_fits(TILE_QUAD, dtype, bsrc)) tile = TILE_QUAD;
+    // ... and its narrower relatives in place of the 128x128 tile, where that one starts a second workgroup per unit and
+    // 256x128 ones fit one round (2560x2048x1024 fp16 18.3 -> 17.0 us, x4096 55.4 -> 45.2; 200x20000x1024 int8 12.5 -> 12.2;
+    // 3x3, 256 channels, 28x28, batch 32, fp16 39.6 -> 33.1, int8 23.7 -> 21.5), or where it starts a third one and 256x192
+    // ones fit (3072x3072x1024 fp16 32.6 -> 25.5).  With fewer 128x128 tiles than units those win (512 channels, 14x14,
+    // batch 32, int8: 26.2 us against 30.6).
+    if (tile == 1 && kchunks >= 64 && tile_fits(TILE_QUAD, dtype, bsrc)) {
+        const long n1 = (long)cdiv(rows, 128) * cdiv(cols, 128);
+        if (n1 > CUS && (long)cdiv(rows, 256) * cdiv(cols, 128) <= CUS) tile = TILE_QUAD + 2;
+        else if (n1 > 2 * CUS && (long)cdiv(rows, 256) * cdiv(cols, 192) <= CUS) tile = TILE_QUAD + 1;
+    }
     const int forced = g_force_tile.load(std::memory_order_relaxed);
     if (forced >= 0 && forced < NUM_TILES) tile = forced;
 
@@ -185,7 +202,8 @@ TileChoice select_tile(int rows, int cols, int kchunks, int dtype, int bsrc, boo
 
 // Relative cost of one tile of the narrower relatives of the 256 x 256 tile, per unit of reduction, in units of the
 // large tile's own cost (measured on matmuls that fill exactly one round of 256 workgroups with each shape).
-static const struct { int tile, bn; double cost; } g_tail_tiles[] = {{10, 192, 0.79}, {11, 128, 0.60}};
+// (tile: next to tile 8; quad: next to TILE_QUAD)
+static const struct { int tile, quad, bn; double cost; } g_tail_tiles[] = {{10, TILE_QUAD + 1, 192, 0.79}, {11, TILE_QUAD + 2, 128, 0.60}};
 
 RangePlan plan_ranges(int rows, int cols, int kchunks, int dtype, int bsrc, bool allow_split, int cb, bool allow_ranges)
 {
@@ -196,7 +214,7 @@ RangePlan plan_ranges(int rows, int cols, int kchunks, int dtype, int bsrc, bool
     p.choice[0] = select_tile(rows, cols, kchunks, dtype, bsrc, allow_split, cb);
     p.choice[1] = p.choice[0];
     if (!allow_ranges || g_force_tile.load(std::memory_order_relaxed) >= 0) return p;
-    if (p.choice[0].tile != 8 || p.choice[0].split_k != 1) return p;
+    if ((p.choice[0].tile != 8 && p.choice[0].tile != TILE_QUAD) || p.choice[0].split_k != 1) return p;
     const int CUS = 256, BN = 256;
     const long tm = cdiv(rows, 256), tn = cdiv(cols, BN), nt = tm * tn;
     if (nt <= CUS || nt % CUS == 0) return p;
@@ -209,7 +227,8 @@ RangePlan plan_ranges(int rows, int cols, int kchunks, int dtype, int bsrc, bool
     double best_cost = 0.92 * plain;                                       // a second launch must pay for itself
     for (unsigned i = 0; i < sizeof g_tail_tiles / sizeof g_tail_tiles[0]; ++i) {
         const long t = tm * cdiv(tail_cols, g_tail_tiles[i].bn);
-        if (t <= CUS && g_tail_tiles[i].cost < best_cost && tile_fits(g_tail_tiles[i].tile, dtype, bsrc)) {
+        const int tile = p.choice[0].tile == TILE_QUAD ? g_tail_tiles[i].quad : g_tail_tiles[i].tile;
+        if (t <= CUS && g_tail_tiles[i].cost < best_cost && tile_fits(tile, dtype, bsrc)) {
             best = (int)i;
             best_cost = g_tail_tiles[i].cost;
         }
@@ -220,7 +239,7 @@ RangePlan plan_ranges(int rows, int cols, int kchunks, int dtype, int bsrc, bool
     p.col_end[0] = (int)c1;
     p.choice[0].workgroups = (int)(n1 * tm);
     p.col_begin[1] = (int)c1;  p.col_end[1] = cols;
-    p.choice[1].tile = g_tail_tiles[best].tile;
+    p.choice[1].tile = p.choice[0].tile == TILE_QUAD ? g_tail_tiles[best].quad : g_tail_tiles[best].tile;
     p.choice[1].split_k = 1;
     p.choice[1].ksteps_per_split = cdiv(kchunks, c.bkb / 16);
     p.choice[1].workgroups = (int)(tm * cdiv(tail_cols, c.bn));

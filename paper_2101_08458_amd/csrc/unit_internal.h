@@ -17,7 +17,8 @@ struct TileCfg {
     int mf;                   // MFMA edge
     int nst;                  // LDS stages
 };
-enum { NUM_TILES = 14, TILE_DEEP = 13 };
+// TILE_QUAD and the two after it: large tiles on four waves (IgemmCfg::QUAD)
+enum { NUM_TILES = 17, TILE_DEEP = 13, TILE_QUAD = 14 };
 extern const TileCfg g_tiles[NUM_TILES];
 extern const TileCfg g_tiles_fp8[NUM_TILES];   // same tiles, wave grids of the fp8 kernels
 
