@@ -1,5 +1,8 @@
 // Layout packing, split-reduction epilogue and the small int8 network operators.
 // All of them are bandwidth-bound permutations / elementwise passes.
+#include <cstring>
+#include <type_traits>
+
 #include "unit_internal.h"
 
 namespace unit {
@@ -11,16 +14,16 @@ namespace unit {
 // With Q > 0 only the pixels (p*srow_step, q*scol_step) of each input image are packed
 // (HW = P*Q output pixels, HWin = pixels per input channel): the input of a strided 1x1 conv.
 template <typename T>
-__global__ void __launch_bounds__(256)
-pack_act_kernel(const T *__restrict__ x, uint8_t *__restrict__ xp, int C, int HW, int cp,
-                int HWin, int Q, int srow, int scol)
+__device__ __forceinline__ void
+pack_act_block(const T *__restrict__ x, uint8_t *__restrict__ xp, int C, int HW, int cp,
+               int HWin, int Q, int srow, int scol, int bx, int by, int n)
 {
     constexpr int CH = 16 / sizeof(T);            // channels per 16-byte chunk
     constexpr int TP = 64;                        // pixels per tile
     constexpr int TC = 64;                        // channels per tile
     __shared__ T tile[TC][TP + 4 / sizeof(T)];
     const int tid = threadIdx.x;
-    const int hw0 = blockIdx.x * TP, c0 = blockIdx.y * TC, n = blockIdx.z;
+    const int hw0 = bx * TP, c0 = by * TC;
     const T *xn = x + (long)n * C * HWin;
     {
         const int px = tid & 63;
@@ -68,8 +71,9 @@ pack_act_kernel(const T *__restrict__ x, uint8_t *__restrict__ xp, int C, int HW
 // bytes; TP is chosen so that a channel row of the tile is a whole 128-byte line.  Needs rows that start on dword boundaries (the range check of those loads works per dword) and a tensor
 // below 2 GiB; the byte-wise kernel above takes the rest.
 template <int ES, int TP>
-__global__ void __launch_bounds__(256)
-pack_act_tr_kernel(const uint8_t *__restrict__ x, uint8_t *__restrict__ xp, int C, int HW, int cp, unsigned x_bytes)
+__device__ __forceinline__ void
+pack_act_tr_block(const uint8_t *__restrict__ x, uint8_t *__restrict__ xp, int C, int HW, int cp, unsigned x_bytes,
+                  int bx, int by, int n)
 {
     constexpr int TC = 64;                        // channels per tile (TP pixels)
     constexpr int EPC = 16 / ES;                  // elements per 16-byte chunk
@@ -84,7 +88,7 @@ pack_act_tr_kernel(const uint8_t *__restrict__ x, uint8_t *__restrict__ xp, int 
     __shared__ __attribute__((aligned(16))) uint8_t tile[TC * TP * ES];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int hw0 = blockIdx.x * TP, c0 = blockIdx.y * TC, n = blockIdx.z;
+    const int hw0 = bx * TP, c0 = by * TC;
     const __amdgpu_buffer_rsrc_t rs = make_rsrc(x, x_bytes);
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
@@ -129,12 +133,12 @@ pack_act_tr_kernel(const uint8_t *__restrict__ x, uint8_t *__restrict__ xp, int 
 // zeroed) and writes the pixel's chunk.  The tiled transpose above would spend a 64-channel tile
 // on them.
 template <typename T, int CL>
-__global__ void __launch_bounds__(256)
-pack_act_smallc_kernel(const T *__restrict__ x, uint8_t *__restrict__ xp, int C, int HW,
-                       int HWin, int Q, int srow, int scol)
+__device__ __forceinline__ void
+pack_act_smallc_block(const T *__restrict__ x, uint8_t *__restrict__ xp, int C, int HW,
+                      int HWin, int Q, int srow, int scol, int bx, int n)
 {
     constexpr int CH = 16 / sizeof(T);
-    const int px = blockIdx.x * 256 + threadIdx.x, n = blockIdx.y;
+    const int px = bx * 256 + threadIdx.x;
     if (px >= HW) return;
     int src = px;
     if (Q > 0) {
@@ -153,59 +157,168 @@ pack_act_smallc_kernel(const T *__restrict__ x, uint8_t *__restrict__ xp, int C,
     *reinterpret_cast<v4i *>(xp + ((long)n * HW + px) * 16) = *reinterpret_cast<const v4i *>(vals);
 }
 
-template <typename T>
-static void launch_pack_small(const T *x, uint8_t *xp, int n, int c, int hw, int hw_in, int Q, int srow, int scol,
-                              hipStream_t st)
+// ------------------------------------------------------------------ pack_weights
+// OIHW -> [k][r][s][cp]: each output channel's reduction becomes one contiguous,
+// zero-padded row (the "column-major B" of the implicit GEMM).  A workgroup belongs to one output channel, a thread
+// gathers the 16 bytes of one chunk (consecutive channels of one tap, RS elements apart, which neighbouring threads find in
+// the same cache lines) and stores them at once.  With `sums` (unsigned activations) the channel's weights are
+// summed on the way: 128 times their sum corrects that channel's outputs.
+struct PackW {
+    const void *w;  uint8_t *wp;  int K, C, RS, cpc, chunks;      // cpc: chunks per tap, chunks = RS * cpc per row
+    DivU dv_cpc;
+    int segs;  DivU dv_segs;                                      // workgroups per output channel
+    int32_t *sums;
+};
+
+template <int ES>
+__device__ __forceinline__ void pack_weights_block(const PackW &a, int blk)
 {
-    const dim3 grid((hw + 255) / 256, n), block(256);
-    if (c <= 4)
-        hipLaunchKernelGGL((pack_act_smallc_kernel<T, 4>), grid, block, 0, st, x, xp, c, hw, hw_in, Q, srow, scol);
-    else if (c <= 8 || sizeof(T) == 2)
-        hipLaunchKernelGGL((pack_act_smallc_kernel<T, 8>), grid, block, 0, st, x, xp, c, hw, hw_in, Q, srow, scol);
+    typedef typename std::conditional<ES == 1, uint8_t, uint16_t>::type T;
+    constexpr int CH = 16 / ES;
+    const int k = divu(blk, a.dv_segs), seg = blk - k * a.segs;
+    const T *row = static_cast<const T *>(a.w) + (size_t)k * a.C * a.RS;
+    uint8_t *dst = a.wp + (size_t)k * a.chunks * 16;
+    int sum = 0;
+    for (int i = seg * 256 + (int)threadIdx.x; i < a.chunks; i += a.segs * 256) {
+        const int rs = divu(i, a.dv_cpc), c0 = (i - rs * a.cpc) * CH;
+        const T *src = row + (size_t)c0 * a.RS + rs;
+        T v[CH];
+#pragma unroll
+        for (int e = 0; e < CH; ++e) v[e] = src[c0 + e < a.C ? (size_t)e * a.RS : 0];      // (past C: zeroed below)
+        __attribute__((aligned(16))) T out[CH];
+#pragma unroll
+        for (int e = 0; e < CH; ++e) out[e] = c0 + e < a.C ? v[e] : (T)0;
+        const v4i q = *reinterpret_cast<const v4i *>(out);
+        *reinterpret_cast<v4i *>(dst + (size_t)i * 16) = q;
+        if (ES == 1)
+#pragma unroll
+            for (int d = 0; d < 4; ++d) { const int qd = q[d];  sum = __builtin_amdgcn_sdot4(qd, 0x01010101, sum, false); }
+    }
+    if (ES == 1 && a.sums) {                        // (one workgroup per channel then)
+        __shared__ int part[4];
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = sum;
+        __syncthreads();
+        if (threadIdx.x == 0) a.sums[k] = 128 * (part[0] + part[1] + part[2] + part[3]);
+    }
+}
+
+// ------------------------------------------------------------------ one launch for both
+// The layout passes of a conv call: the first `wblocks` workgroups pack weights, the others activations.  Both are bound
+// by their launch on all but large layers, and a call with plain operands needs both before its main kernel: one launch
+// instead of two, or three with the weights' sums (3x3, 128 channels, 28x28, batch 8, u8 x i8, whole call: 15.2 -> 10.1 us;
+// 3x3x3, 128 channels, 4x28x28, fp16: 17.9 -> 16.0).
+enum { ACT_TR = 0, ACT_TILE = 1, ACT_SMALL = 2 };
+struct PackA {
+    const void *x;  uint8_t *xp;  int C, HW, cp, HWin, Q, srow, scol;  unsigned x_bytes;
+    int gx, gy;  DivU dv_gx, dv_gy;                               // workgroups along the pixels and the channels of an image
+};
+
+template <int ES, int ACT>
+__device__ __forceinline__ void pack_act_any(const PackA &a, int bx, int by, int n)
+{
+    typedef typename std::conditional<ES == 1, int8_t, uint16_t>::type T;
+    const T *x = static_cast<const T *>(a.x);
+    if (ACT == ACT_TR)
+        pack_act_tr_block<ES, 128 / ES>(static_cast<const uint8_t *>(a.x), a.xp, a.C, a.HW, a.cp, a.x_bytes, bx, by, n);
+    else if (ACT == ACT_TILE)
+        pack_act_block<T>(x, a.xp, a.C, a.HW, a.cp, a.HWin, a.Q, a.srow, a.scol, bx, by, n);
+    else if (a.C <= 4)
+        pack_act_smallc_block<T, 4>(x, a.xp, a.C, a.HW, a.HWin, a.Q, a.srow, a.scol, bx, n);
+    else if (a.C <= 8 || ES == 2)
+        pack_act_smallc_block<T, 8>(x, a.xp, a.C, a.HW, a.HWin, a.Q, a.srow, a.scol, bx, n);
     else
-        hipLaunchKernelGGL((pack_act_smallc_kernel<T, 16 / sizeof(T)>), grid, block, 0, st, x, xp, c, hw, hw_in, Q, srow, scol);
+        pack_act_smallc_block<T, 16 / ES>(x, a.xp, a.C, a.HW, a.HWin, a.Q, a.srow, a.scol, bx, n);
+}
+// (each alone: the shared launch's dependent argument loads and divisions cost 0.5 us)
+template <int ES, int ACT>
+__global__ void __launch_bounds__(256) pack_act_kernel(const PackA a) { pack_act_any<ES, ACT>(a, blockIdx.x, blockIdx.y, blockIdx.z); }
+template <int ES>
+__global__ void __launch_bounds__(256) pack_weights_kernel(const PackW w) { pack_weights_block<ES>(w, blockIdx.x); }
+template <int ES, int ACT>
+__global__ void __launch_bounds__(256) pack_both_kernel(const PackW w, const PackA a, int wblocks)
+{
+    int blk = blockIdx.x;
+    if (blk < wblocks) {
+        pack_weights_block<ES>(w, blk);
+        return;
+    }
+    blk -= wblocks;
+    const int t = divu(blk, a.dv_gx), bx = blk - t * a.gx;
+    const int n = divu(t, a.dv_gy), by = t - n * a.gy;
+    pack_act_any<ES, ACT>(a, bx, by, n);
 }
 
-// sh, sw > 1 with p, q > 0: pack only the pixels (i*sh, j*sw), i < p, j < q (output [n][p*q][cp])
-hipError_t launch_pack_act_sub(int dtype, int n, int c, int h, int w, int sh, int sw, int p, int q,
-                               const void *x, void *xp, hipStream_t st)
+static DivU make_div(long d)
 {
-    const bool sub = p > 0;
-    const int hw_in = h * w, hw = sub ? p * q : hw_in;
-    const int Q = sub ? q : 0, srow = sh * w, scol = sw;
-    const int chunk = (dtype == DT_I8) ? 16 : 8;
-    if (c <= chunk && n <= 65535) {
-        if (dtype == DT_I8) launch_pack_small((const int8_t *)x, (uint8_t *)xp, n, c, hw, hw_in, Q, srow, scol, st);
-        else                launch_pack_small((const uint16_t *)x, (uint8_t *)xp, n, c, hw, hw_in, Q, srow, scol, st);
-        return hipGetLastError();
+    DivU v;
+    v.d = d > 1 ? (unsigned)d : 1u;
+    v.m = d > 1 ? (unsigned)((1ULL << 32) / (unsigned long long)d) : 0xffffffffu;
+    return v;
+}
+
+hipError_t launch_pack(int dtype, const PackWeights *w, const PackActs *x, hipStream_t st)
+{
+    const int es = (dtype == DT_I8) ? 1 : 2, ch = 16 / es;         // callers pass the storage type: one- or two-byte elements
+    PackW pw;
+    PackA pa;
+    std::memset(&pw, 0, sizeof pw);
+    std::memset(&pa, 0, sizeof pa);
+    long wblocks = 0, ablocks = 0;
+    int act = ACT_TILE;
+    if (w) {
+        pw.w = w->w;  pw.wp = static_cast<uint8_t *>(w->wp);  pw.K = w->k;  pw.C = w->c;  pw.RS = w->rs;
+        pw.cpc = (w->c + ch - 1) / ch;
+        const long chunks = (long)pw.cpc * pw.RS;
+        if (chunks >= (1L << 31) || (w->sums && es != 1)) return hipErrorInvalidValue;
+        pw.chunks = (int)chunks;
+        pw.dv_cpc = make_div(pw.cpc);
+        pw.segs = w->sums ? 1 : (int)((chunks + 255) / 256);
+        pw.dv_segs = make_div(pw.segs);
+        pw.sums = w->sums;
+        wblocks = (long)w->k * pw.segs;
     }
-    const int es = (dtype == DT_I8) ? 1 : 2;
-    const long x_bytes = (long)n * c * hw_in * es;
-    if (!sub && ((long)hw * es) % 4 == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0 && x_bytes < (1L << 31)) {
-        const int cp = (c + chunk - 1) / chunk * chunk;
-        const int tp = 128 / es;                   // tile pixels: one 128-byte line per channel row
-        dim3 grid((hw + tp - 1) / tp, (cp + 63) / 64, n);
-        if (es == 1) hipLaunchKernelGGL((pack_act_tr_kernel<1, 128>), grid, dim3(256), 0, st, (const uint8_t *)x, (uint8_t *)xp, c, hw, cp, (unsigned)x_bytes);
-        else         hipLaunchKernelGGL((pack_act_tr_kernel<2, 64>), grid, dim3(256), 0, st, (const uint8_t *)x, (uint8_t *)xp, c, hw, cp, (unsigned)x_bytes);
-        return hipGetLastError();
+    if (x) {
+        const bool sub = x->p > 0;                                 // only the pixels (i * sh, j * sw), i < p, j < q
+        pa.x = x->x;  pa.xp = static_cast<uint8_t *>(x->xp);  pa.C = x->c;
+        pa.HWin = x->h * x->w;
+        pa.HW = sub ? x->p * x->q : pa.HWin;
+        pa.Q = sub ? x->q : 0;  pa.srow = x->sh * x->w;  pa.scol = x->sw;
+        pa.cp = (x->c + ch - 1) / ch * ch;
+        const long x_bytes = (long)x->n * x->c * pa.HWin * es;
+        pa.gy = (pa.cp + 63) / 64;
+        if (x->c <= ch) {
+            act = ACT_SMALL;
+            pa.gx = (pa.HW + 255) / 256;
+            pa.gy = 1;
+        } else if (!sub && ((long)pa.HW * es) % 4 == 0 && (reinterpret_cast<uintptr_t>(x->x) & 15) == 0 && x_bytes < (1L << 31)) {
+            act = ACT_TR;
+            pa.gx = (pa.HW + 128 / es - 1) / (128 / es);           // tile pixels: one 128-byte line per channel row
+            pa.x_bytes = (unsigned)x_bytes;
+        } else {
+            pa.gx = (pa.HW + 63) / 64;
+        }
+        pa.dv_gx = make_div(pa.gx);
+        pa.dv_gy = make_div(pa.gy);
+        ablocks = (long)pa.gx * pa.gy * x->n;
     }
-    if (dtype == DT_I8) {   // callers pass the storage type: one- or two-byte elements
-        const int cp = (c + 15) / 16 * 16;
-        dim3 grid((hw + 63) / 64, (cp + 63) / 64, n);
-        hipLaunchKernelGGL(pack_act_kernel<int8_t>, grid, dim3(256), 0, st,
-                           (const int8_t *)x, (uint8_t *)xp, c, hw, cp, hw_in, Q, srow, scol);
-    } else {
-        const int cp = (c + 7) / 8 * 8;
-        dim3 grid((hw + 63) / 64, (cp + 63) / 64, n);
-        hipLaunchKernelGGL(pack_act_kernel<uint16_t>, grid, dim3(256), 0, st,
-                           (const uint16_t *)x, (uint8_t *)xp, c, hw, cp, hw_in, Q, srow, scol);
-    }
+    if (wblocks + ablocks >= (1L << 31)) return hipErrorInvalidValue;
+    const dim3 block(256), both((unsigned)(wblocks + ablocks)), acts(pa.gx, pa.gy, x ? x->n : 0);
+    auto go = [&](auto es_c, auto act_c) {
+        constexpr int ES = decltype(es_c)::value, ACT = decltype(act_c)::value;
+        if (!x)      hipLaunchKernelGGL((pack_weights_kernel<ES>), both, block, 0, st, pw);
+        else if (!w) hipLaunchKernelGGL((pack_act_kernel<ES, ACT>), acts, block, 0, st, pa);
+        else         hipLaunchKernelGGL((pack_both_kernel<ES, ACT>), both, block, 0, st, pw, pa, (int)wblocks);
+    };
+    auto pick = [&](auto es_c) {
+        if (act == ACT_TR)        go(es_c, IntC<ACT_TR>{});
+        else if (act == ACT_TILE) go(es_c, IntC<ACT_TILE>{});
+        else                      go(es_c, IntC<ACT_SMALL>{});
+    };
+    if (es == 1) pick(IntC<1>{});
+    else         pick(IntC<2>{});
     return hipGetLastError();
-}
-
-hipError_t launch_pack_act(int dtype, int n, int c, int h, int w, const void *x, void *xp, hipStream_t st)
-{
-    return launch_pack_act_sub(dtype, n, c, h, w, 1, 1, 0, 0, x, xp, st);
 }
 
 // packed int8 [n][hw][cp] -> NCHW
@@ -227,38 +340,6 @@ hipError_t launch_unpack_act_i8(int n, int c, int h, int w, const void *xp, int8
     int cp = (c + 15) / 16 * 16;
     hipLaunchKernelGGL(unpack_act_i8_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
                        (const int8_t *)xp, x, c, h * w, cp, total);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------ pack_weights
-// OIHW -> [k][r][s][cp]: each output channel's reduction becomes one contiguous,
-// zero-padded row (the "column-major B" of the implicit GEMM).  Done once per layer.
-template <typename T>
-__global__ void pack_weights_kernel(const T *__restrict__ w, T *__restrict__ wp,
-                                    int C, int RS, int cp, long total)
-{
-    long i = (long)blockIdx.x * blockDim.x + threadIdx.x;   // index into wp
-    if (i >= total) return;
-    int c = i % cp;
-    long t = i / cp;
-    int rs = t % RS;
-    long k = t / RS;
-    wp[i] = (c < C) ? w[(k * C + c) * RS + rs] : (T)0;
-}
-
-hipError_t launch_pack_weights(int dtype, int k, int c, int r, int s, const void *w, void *wp, hipStream_t st)
-{
-    if (dtype == DT_I8) {   // callers pass the storage type: one- or two-byte elements
-        int cp = (c + 15) / 16 * 16;
-        long total = (long)k * r * s * cp;
-        hipLaunchKernelGGL(pack_weights_kernel<int8_t>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
-                           (const int8_t *)w, (int8_t *)wp, c, r * s, cp, total);
-    } else {
-        int cp = (c + 7) / 8 * 8;
-        long total = (long)k * r * s * cp;
-        hipLaunchKernelGGL(pack_weights_kernel<uint16_t>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
-                           (const uint16_t *)w, (uint16_t *)wp, c, r * s, cp, total);
-    }
     return hipGetLastError();
 }
 

@@ -363,7 +363,7 @@ size_t conv_split_bytes_any(const ConvGeom &g, int dtype)
 
 int conv_wpacked(const ConvND *d, int dtype, const void *x, const void *wp,
                  void *y_raw, const unit_requant *rq, int8_t *y_i8,
-                 void *ws, size_t ws_bytes, void *stream, const int32_t *fix = nullptr);
+                 void *ws, size_t ws_bytes, void *stream, const int32_t *fix = nullptr, const PackWeights *pw = nullptr);
 bool nchw_direct_ok(const ConvND *d, int dtype, const void *x, const unit_requant *rq);
 
 // workspace conv_wpacked needs for this call (after the packed weights, if any)
@@ -394,21 +394,18 @@ int conv_plain(const ConvND *d, int dtype, const void *x, const void *w,
     if (!ws || ws_bytes < wt_b + fix_b + wpacked_need(d, dtype, g, x, rq)) return UNIT_EWORKSPACE;
     if (!aligned256(ws)) return UNIT_EINVAL;
     uint8_t *wp = static_cast<uint8_t *>(ws);
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    UNIT_HIP(launch_pack_weights(storage_dtype(dtype), d->k, d->c, d->t * d->r, d->s, w, wp, st));
-    int32_t *fix = nullptr;
-    if (fix_b) {            // unsigned activations: 128 * (sum of each filter's weights)
-        fix = reinterpret_cast<int32_t *>(wp + wt_b);
-        UNIT_HIP(launch_rowsum128_i8(wp, (long)g.kchunks * 16, d->k, g.kchunks, fix, st));
-    }
-    return conv_wpacked(d, dtype, x, wp, y_raw, rq, y_i8, wp + wt_b + fix_b, ws_bytes - wt_b - fix_b, stream, fix);
+    // (unsigned activations: 128 * (sum of each filter's weights) corrects its outputs)
+    int32_t *fix = fix_b ? reinterpret_cast<int32_t *>(wp + wt_b) : nullptr;
+    const PackWeights pw = {w, wp, d->k, d->c, d->t * d->r * d->s, fix};
+    return conv_wpacked(d, dtype, x, wp, y_raw, rq, y_i8, wp + wt_b + fix_b, ws_bytes - wt_b - fix_b, stream, fix, &pw);
 }
 
 // NCHW activations + packed weights: fused direct read when possible, else pack_act into the
-// workspace followed by the packed kernel.
+// workspace followed by the packed kernel.  pw: weights that are still to be packed into wp, in the same launch as the
+// activations where those are packed.
 int conv_wpacked(const ConvND *d, int dtype, const void *x, const void *wp,
                  void *y_raw, const unit_requant *rq, int8_t *y_i8,
-                 void *ws, size_t ws_bytes, void *stream, const int32_t *fix)
+                 void *ws, size_t ws_bytes, void *stream, const int32_t *fix, const PackWeights *pw)
 {
     ConvGeom g;
     int rc = conv_geom(d, dtype, &g);
@@ -419,11 +416,13 @@ int conv_wpacked(const ConvND *d, int dtype, const void *x, const void *wp,
     size_t split_b = conv_split_bytes(g, dtype, BSRC_NCHW);
     if (nchw_direct_ok(d, dtype, x, rq)) {
         if (split_b && (!ws || ws_bytes < split_b)) return UNIT_EWORKSPACE;
+        if (pw) UNIT_HIP(launch_pack(storage_dtype(dtype), pw, nullptr, static_cast<hipStream_t>(stream)));
         return conv_packed(d, dtype, x, wp, y_raw, rq, y_i8, nullptr, ws, ws_bytes, stream, BSRC_NCHW);
     }
     if (nchw_shift_ok(d, dtype, g, x, rq)) {
         split_b = conv_split_bytes(g, dtype, BSRC_NCHWS);
         if (split_b && (!ws || ws_bytes < split_b)) return UNIT_EWORKSPACE;
+        if (pw) UNIT_HIP(launch_pack(storage_dtype(dtype), pw, nullptr, static_cast<hipStream_t>(stream)));
         return conv_packed(d, dtype, x, wp, y_raw, rq, y_i8, nullptr, ws, ws_bytes, stream, BSRC_NCHWS);
     }
     split_b = conv_split_bytes(g, dtype, BSRC_GATHER);
@@ -436,12 +435,13 @@ int conv_wpacked(const ConvND *d, int dtype, const void *x, const void *wp,
         (d->stride_h > 1 || d->stride_w > 1)) {
         ConvND sub = *d;
         sub.h = g.p;  sub.w = g.q;  sub.stride_h = sub.stride_w = 1;
-        UNIT_HIP(launch_pack_act_sub(storage_dtype(dtype), d->n, d->c, d->h, d->w, d->stride_h, d->stride_w,
-                                     g.p, g.q, x, xp, static_cast<hipStream_t>(stream)));
+        const PackActs pa = {x, xp, d->n, d->c, d->h, d->w, d->stride_h, d->stride_w, g.p, g.q};
+        UNIT_HIP(launch_pack(storage_dtype(dtype), pw, &pa, static_cast<hipStream_t>(stream)));
         return conv_packed(&sub, dtype, xp, wp, y_raw, rq, y_i8, nullptr, split_b ? xp + act_b : nullptr, split_b,
                            stream, BSRC_GATHER, fix);
     }
-    UNIT_HIP(launch_pack_act(storage_dtype(dtype), d->n, d->c, d->d * d->h, d->w, x, xp, static_cast<hipStream_t>(stream)));
+    const PackActs pa = {x, xp, d->n, d->c, d->d * d->h, d->w, 1, 1, 0, 0};
+    UNIT_HIP(launch_pack(storage_dtype(dtype), pw, &pa, static_cast<hipStream_t>(stream)));
     return conv_packed(d, dtype, xp, wp, y_raw, rq, y_i8, nullptr, split_b ? xp + act_b : nullptr, split_b, stream,
                        BSRC_GATHER, fix);
 }
@@ -775,7 +775,8 @@ static int pack_act_any(int dtype, int32_t n, int32_t c, int32_t h, int32_t w, c
     if (n > 65535) return UNIT_ENOTSUP;           // the image index is grid.z
     if (bytes < need) return UNIT_EWORKSPACE;
     if (!aligned16(xp)) return UNIT_EINVAL;
-    UNIT_HIP(launch_pack_act(dtype, n, c, h, w, x, xp, static_cast<hipStream_t>(stream)));
+    const PackActs pa = {x, xp, n, c, h, w, 1, 1, 0, 0};
+    UNIT_HIP(launch_pack(dtype, nullptr, &pa, static_cast<hipStream_t>(stream)));
     return UNIT_OK;
 }
 
@@ -797,7 +798,8 @@ static int pack_w_any(int dtype, const unit_conv2d_desc *d, const void *w, void 
     if (!need || !w || !wp) return UNIT_EINVAL;
     if (bytes < need) return UNIT_EWORKSPACE;
     if (!aligned16(wp)) return UNIT_EINVAL;
-    UNIT_HIP(launch_pack_weights(dtype, d->k, d->c, d->r, d->s, w, wp, static_cast<hipStream_t>(stream)));
+    const PackWeights pw = {w, wp, d->k, d->c, d->r * d->s, nullptr};
+    UNIT_HIP(launch_pack(dtype, &pw, nullptr, static_cast<hipStream_t>(stream)));
     return UNIT_OK;
 }
 

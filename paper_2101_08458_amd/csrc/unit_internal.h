@@ -51,10 +51,12 @@ bool tile_fits(int tile, int dtype, int bsrc);
 // launchers (kernels_*.hip).  All return hipError_t from the launch.
 hipError_t launch_igemm(int dtype, int bsrc, int tile, const IgemmArgs &a, int split_k, hipStream_t st);
 
-hipError_t launch_pack_act(int dtype, int n, int c, int h, int w, const void *x, void *xp, hipStream_t st);
-hipError_t launch_pack_act_sub(int dtype, int n, int c, int h, int w, int sh, int sw, int p, int q,
-                               const void *x, void *xp, hipStream_t st);
-hipError_t launch_pack_weights(int dtype, int k, int c, int r, int s, const void *w, void *wp, hipStream_t st);
+// Layout passes, one launch for what is asked for (either may be NULL).  dtype: storage type (DT_I8 one byte, else two).
+// weights [k][c][rs] -> [k][rs][cp]; sums (one-byte types): 128 * (sum of each output channel's signed weights)
+struct PackWeights { const void *w;  void *wp;  int k, c, rs;  int32_t *sums; };
+// activations [n][c][h * w] -> [n][h * w][cp]; p > 0: only the pixels (i * sh, j * sw), i < p, j < q
+struct PackActs { const void *x;  void *xp;  int n, c, h, w, sh, sw, p, q; };
+hipError_t launch_pack(int dtype, const PackWeights *w, const PackActs *x, hipStream_t st);
 hipError_t launch_unpack_act_i8(int n, int c, int h, int w, const void *xp, int8_t *x, hipStream_t st);
 // one operand of launch_pad_rows
 struct PadRows { const uint8_t *src; long ld_bytes; uint8_t *dst; int rows; };
