@@ -9,7 +9,7 @@ unit, written by the Makefile) and fails when a variant that uses the inline-ass
 or spilled vector registers.  Variants that keep the compiler's builtins (32-byte fragments on wave windows of eight or more
 MFMA tiles: igemm.hpp, ASM_TR) may spill and are only listed.
 
-The 256-row tiles of 16x16 accumulators issue their MFMAs as inline assembly, whose operands must not be written by
+The tiles of 128 rows and more with 16x16 accumulators issue their MFMAs as inline assembly, whose operands must not be written by
 vector instructions just before; a spilled register would be copied there, so those kernels must not spill either.
 
 usage: check_resources.py FILE.res [FILE.res ...]      exit status 1 on a violation
@@ -41,7 +41,7 @@ def main(paths):
     for p in paths:
         for k in list(kernels(p)):
             dt, bm, bn, bkb, wgm, wgn, wgk, mf, nst, occ, bsrc, epi = k["args"]
-            if mf == 16 and bm == 256 and int(k.get("VGPRs Spill", "0")):
+            if mf == 16 and bm >= 128 and int(k.get("VGPRs Spill", "0")):
                 quad.append((p, k["args"], int(k["VGPRs Spill"])))
             if bsrc not in DIRECT:
                 continue

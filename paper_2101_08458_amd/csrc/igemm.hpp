@@ -351,9 +351,11 @@ struct IgemmCfg {
         LPT   = IA + IB,
         STAGE_BYTES  = (BM + BN) * BKB,
         EDGE_BYTES   = (BSRC == BSRC_NCHWS || BSRC == BSRC_NCHWE) ? 1024 : 0,   // direct reads: first and last 16 bytes of the tensor
-        // 256 rows of 16x16 accumulators on four waves: the loop with pinned accumulators and three buffers of A
-        QUAD  = (MF == 16 && BM == 256 && NW == 4) ? 1 : 0,
-        RING_BYTES   = QUAD ? 3 * BM * BKB + 2 * BN * BKB : NST * STAGE_BYTES + EDGE_BYTES,
+        // 16x16 accumulators in large windows: the loop with pinned accumulators (QUAD), on 256 rows and four waves with
+        // three buffers of A and two of B, on 128 rows with a ring of four stages
+        QUAD  = (MF == 16 && WGK == 1 && ((BM == 256 && NW == 4) || (BM == 128 && NST == 4))) ? 1 : 0,
+        RING4 = (QUAD && NST == 4) ? 1 : 0,
+        RING_BYTES   = (QUAD && !RING4) ? 3 * BM * BKB + 2 * BN * BKB : NST * STAGE_BYTES + EDGE_BYTES,
         REDUCE_BYTES = (WGK > 1) ? WGK * BM * BN * 4 : 0,
         // int8 NCHW results wait in LDS behind the partial sums (free once the main loop is done); the 32 bytes of
         // padding spread the eight rows a wave writes at once over all banks (tiles of 32 columns: over half of them, two
@@ -1048,9 +1050,10 @@ igemm_kernel(const IgemmArgs g)
     };
 
     if (ks_begin < ks_end) {
-        constexpr int AHEAD = WHOLE ? NST - 1 : NST;            // tiles in flight after the prologue
-        // QUAD: three buffers of A, then two of B
-        constexpr int A_SZ = BM * BKB, B_SZ = BN * BKB, B_AT = 3 * A_SZ;
+        constexpr int AHEAD = (WHOLE || C::RING4) ? NST - 1 : NST;  // tiles in flight after the prologue
+        // QUAD: the buffers of A, then those of B
+        constexpr int NBUF_A = C::RING4 ? 4 : 3, NBUF_B = C::RING4 ? 4 : 2;
+        constexpr int A_SZ = BM * BKB, B_SZ = BN * BKB, B_AT = NBUF_A * A_SZ;
         if ((BSRC == BSRC_NCHWS || EDGE1) && wave == 0)   // first and last 16 bytes of the tensor (see read_frags)
             dma16(rsB, smem + NST * C::STAGE_BYTES,
                   lane == 0 ? 0u : lane == 1 ? (unsigned)(g.b_bytes - 16) : UNIT_OOB);
@@ -1097,25 +1100,35 @@ igemm_kernel(const IgemmArgs g)
             // evenly between the MFMAs by hand: the loads of a step, issued in one half of it, stall the wave at the
             // memory pipe (2930 cycles a step against 2550).  That needs a third buffer of A: its tile two steps ahead
             // streams in during the first half of a step, B's during the second, when B's buffer is free.
-            static_assert(!QUAD || (C::NKSUB == 2 && WGK == 1 && NST == 2 && FW == 1), "two sub-steps, whole accumulators");
+            // On 128x128 (one workgroup per unit, four stages of both operands, tiles three steps ahead) the same loop runs
+            // on eight waves of 64x32 windows: with 32 MFMAs a step or fewer a lone wave per SIMD cannot cover its
+            // barriers (fp16 1536x2048x1792 19.0 us on the register-prefetch loop with 32x32 MFMAs, 17.2 on four
+            // waves here, 16.7 on eight; 2048x2048x4096 40.7 / 36.0 / 36.4; int8 1536x1536x4096 18.4 / 16.4 / 15.8).
+            static_assert(!QUAD || (C::NKSUB == 2 && (NST == 2 || C::RING4) && FW == 1), "two sub-steps, whole accumulators");
             static_assert(BSRC == BSRC_PLAIN || MASKED, "B from plain rows or a masked gather");
             constexpr int NM = TM * TN, NR = TM + TN;
             constexpr int R_EVERY = (NM * 3 / 4) / NR, A_EVERY = NM / IA, B_EVERY = NM / IB;
-            static_assert(R_EVERY >= 2 && A_EVERY * IA <= NM && B_EVERY * IB <= NM, "every read and load has its place");
+            static_assert(R_EVERY >= 1 && A_EVERY * IA <= NM && B_EVERY * IB <= NM, "every read and load has its place");
             auto read_one = [&](int at_a, int at_b, int sub, int slot, int x) {
                 const int ch = sub * C::CPL + lchunk;
                 if (x < TN) fb[slot][x] = Frag<FW>::load(smem + at_b + (b_row + x * MF) * BKB, ch, b_swz);
                 else        fa[slot][x - TN] = Frag<FW>::load(smem + at_a + (a_row + (x - TN) * MF) * BKB, ch, a_swz);
             };
-            int a0 = 0, a1 = A_SZ, a2 = 2 * A_SZ, b0 = B_AT, b1 = B_AT + B_SZ;
+            int at_a[NBUF_A], at_b[NBUF_B];         // buffers of the tile being multiplied, the next one, ...
 #pragma unroll
-            for (int x = 0; x < NR; ++x) read_one(a0, b0, 0, 0, x);
+            for (int t = 0; t < NBUF_A; ++t) at_a[t] = t * A_SZ;
+#pragma unroll
+            for (int t = 0; t < NBUF_B; ++t) at_b[t] = B_AT + t * B_SZ;
+            // (two buffers of B: the next tile but one goes where this step's was read, after the barrier)
+            constexpr int FILL_A = NBUF_A - 1, FILL_B = C::RING4 ? 3 : 0;
+#pragma unroll
+            for (int x = 0; x < NR; ++x) read_one(at_a[0], at_b[0], 0, 0, x);
             for (int ks = ks_begin; ks < ks_end; ++ks) {
                 issue_begin();
 #pragma unroll
                 for (int half = 0; half < 2; ++half) {
                     if (half) {
-                        UNIT_WAIT_VM_LGKM0(IA);         // own part of the next tile landed, own reads of this one done
+                        UNIT_WAIT_VM_LGKM0((C::RING4 ? C::LPT : 0) + IA);       // own part of the next tile landed, own reads of this one done
                         UNIT_BARRIER();
                     }
                     __builtin_amdgcn_sched_barrier(0);
@@ -1124,21 +1137,25 @@ igemm_kernel(const IgemmArgs g)
                         // (back and forth through the columns: an MFMA keeps one operand of the one before it)
                         const int i = r / TN, j = (i & 1) ? TN - 1 - r % TN : r % TN;
                         M::run_acc(acc[i][j], fa[half][i], fb[half][j]);
-                        if (r % R_EVERY == R_EVERY - 2 && r / R_EVERY < NR) {
-                            if (!half) read_one(a0, b0, 1, 1, r / R_EVERY);
-                            else       read_one(a1, b1, 0, 0, r / R_EVERY);
+                        if (r % R_EVERY == (R_EVERY > 1 ? R_EVERY - 2 : 0) && r / R_EVERY < NR) {
+                            if (!half) read_one(at_a[0], at_b[0], 1, 1, r / R_EVERY);
+                            else       read_one(at_a[1], at_b[1], 0, 0, r / R_EVERY);
                         }
                         if (!half && r % A_EVERY == A_EVERY / 2 && r / A_EVERY < IA)
-                            dma16s(rsA, smem + a2 + wave * 1024 + (r / A_EVERY) * NW * 1024, offA[r / A_EVERY], so);
+                            dma16s(rsA, smem + at_a[FILL_A] + wave * 1024 + (r / A_EVERY) * NW * 1024, offA[r / A_EVERY], so);
                         if (half && r % B_EVERY == B_EVERY / 2 && r / B_EVERY < IB)
-                            issue_b(smem + b0 + wave * 1024 + (r / B_EVERY) * NW * 1024, r / B_EVERY);
+                            issue_b(smem + at_b[FILL_B] + wave * 1024 + (r / B_EVERY) * NW * 1024, r / B_EVERY);
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 }
                 issue_next();
-                const int ta = a0, tb = b0;
-                a0 = a1;  a1 = a2;  a2 = ta;
-                b0 = b1;  b1 = tb;
+                const int ta = at_a[0], tb = at_b[0];
+#pragma unroll
+                for (int t = 0; t + 1 < NBUF_A; ++t) at_a[t] = at_a[t + 1];
+#pragma unroll
+                for (int t = 0; t + 1 < NBUF_B; ++t) at_b[t] = at_b[t + 1];
+                at_a[NBUF_A - 1] = ta;
+                at_b[NBUF_B - 1] = tb;
             }
             acc_wait();
 #pragma unroll

@@ -14,6 +14,7 @@ namespace unit {
     {BM, BN, BKB, WGM, WGN, WGK, MF, NST},
 #define UNIT_TILE_PLAIN UNIT_TILE_CASE
 #define UNIT_TILE_QUAD UNIT_TILE_CASE
+#define UNIT_TILE_RING UNIT_TILE_CASE
 #define UNIT_TILE_NONE(ID) {0, 0, 0, 0, 0, 0, 0, 0},
 const TileCfg g_tiles[NUM_TILES] = {
 #include "tiles.def"
@@ -24,6 +25,7 @@ const TileCfg g_tiles_fp8[NUM_TILES] = {
 #undef UNIT_TILE_CASE
 #undef UNIT_TILE_PLAIN
 #undef UNIT_TILE_QUAD
+#undef UNIT_TILE_RING
 #undef UNIT_TILE_NONE
 
 // Process-wide override of the rule (unit_debug_force_tile): -1 = none.  Set by tests and tuning

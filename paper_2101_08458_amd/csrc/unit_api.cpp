@@ -128,7 +128,8 @@ int conv_geom(const ConvND *d, int dtype, ConvGeom *g)
 void fill_tile_info(const RangePlan &p, int dtype, unit_tile_info *out)
 {
     const TileChoice &ch = p.choice[0];
-    const TileCfg *tiles = dtype == UNIT_FP8 ? g_tiles_fp8 : g_tiles;
+    // (u8 x i8 runs the four-stage tile on the waves of the fp8 one)
+    const TileCfg *tiles = (dtype == UNIT_FP8 || (dtype == UNIT_U8I8 && ch.tile == TILE_DEEP)) ? g_tiles_fp8 : g_tiles;
     const TileCfg &c = tiles[ch.tile];
     out->block_m = c.bm;  out->block_n = c.bn;  out->block_k_bytes = c.bkb;
     out->waves_m = c.wgm; out->waves_n = c.wgn; out->waves_k = c.wgk;
