@@ -344,8 +344,8 @@ hipError_t launch_unpack_act_i8(int n, int c, int h, int w, const void *xp, int8
 }
 
 // ------------------------------------------------------------------ pad_rows
-// Copies one or two [rows][row_bytes] matrices (row pitch ld_bytes, any alignment) into dense
-// [rows][row_chunks * 16 bytes] ones, zero filling the tail: matmul operands that do not meet the
+// Copies one or two [rows][row_bytes] matrices (row pitch ld_bytes, any alignment) into
+// [rows][row_chunks * 16 bytes] ones of row pitch dst_ld, zero filling the tail: matmul operands that do not meet the
 // 16-byte rule of the main kernel.  Bound by memory traffic and by the launch, so a thread moves a whole 16-byte
 // chunk (the source needs no alignment), only the last chunk of a row, which may cross its end, is collected byte by
 // byte, and both operands of a product go in one launch (grid.y).  Before, a thread moved one byte, after a 64-bit
@@ -353,17 +353,17 @@ hipError_t launch_unpack_act_i8(int n, int c, int h, int w, const void *xp, int8
 // (Both operands get the block count of the larger one, and the smaller one's spare workgroups leave at once; a few rows
 // against a large matrix still gain: 32 x 4097 x 4095 in fp16, 63.8 -> 26.3 us as a whole.)
 __global__ void __launch_bounds__(256)
-pad_rows_kernel(const PadRows p0, const PadRows p1, int row_bytes, unsigned row_chunks)
+pad_rows_kernel(const PadRows p0, const PadRows p1, int row_bytes, DivU row_chunks)
 {
     const bool second = blockIdx.y != 0;
     const uint8_t *src = second ? p1.src : p0.src;
     uint8_t *dst = second ? p1.dst : p0.dst;
-    const long ld_bytes = second ? p1.ld_bytes : p0.ld_bytes;
-    const long total = (long)(second ? p1.rows : p0.rows) * row_chunks;
+    const long ld_bytes = second ? p1.ld_bytes : p0.ld_bytes, dst_ld = second ? p1.dst_ld : p0.dst_ld;
+    const long total = (long)(second ? p1.rows : p0.rows) * row_chunks.d;
     const long i = (long)blockIdx.x * 256 + threadIdx.x;
     if (i >= total) return;
-    const long r = (total >> 32) ? i / row_chunks : (long)((unsigned)i / row_chunks);
-    const int b = (int)(i - r * row_chunks) * 16;
+    const long r = (total >> 31) ? i / row_chunks.d : (long)divu((int)i, row_chunks);
+    const int b = (int)(i - r * row_chunks.d) * 16;
     const uint8_t *s = src + r * ld_bytes + b;
     uint4 w;
     if (b + 16 <= row_bytes) {
@@ -375,7 +375,7 @@ pad_rows_kernel(const PadRows p0, const PadRows p1, int row_bytes, unsigned row_
             if (b + e < row_bytes) t[e >> 2] |= (unsigned)s[e] << (8 * (e & 3));
         w = make_uint4(t[0], t[1], t[2], t[3]);
     }
-    *reinterpret_cast<uint4 *>(dst + i * 16) = w;
+    *reinterpret_cast<uint4 *>(dst + r * dst_ld + b) = w;
 }
 
 hipError_t launch_pad_rows(const PadRows *ops, int nops, int row_bytes, int row_chunks, hipStream_t st)
@@ -383,7 +383,7 @@ hipError_t launch_pad_rows(const PadRows *ops, int nops, int row_bytes, int row_
     const PadRows &p0 = ops[0], &p1 = ops[nops - 1];
     const long rows = p0.rows > p1.rows ? p0.rows : p1.rows;
     hipLaunchKernelGGL(pad_rows_kernel, dim3((unsigned)((rows * row_chunks + 255) / 256), nops), dim3(256), 0, st,
-                       p0, p1, row_bytes, (unsigned)row_chunks);
+                       p0, p1, row_bytes, make_div(row_chunks));
     return hipGetLastError();
 }
 

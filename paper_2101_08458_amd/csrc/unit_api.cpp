@@ -447,14 +447,26 @@ int conv_wpacked(const ConvND *d, int dtype, const void *x, const void *wp,
                        BSRC_GATHER, fix);
 }
 
+// Row pitch of an operand's copy: whole 128-byte lines, so that a step's 128 bytes of a row are one line and not two halves
+// (1533x2001x1777 fp16, whole call: 28.0 -> 23.5 us), and no multiple of 4 KiB, whose rows would start in the same
+// cache channel.
+inline long copy_pitch(int kpad_bytes)
+{
+    long p = ((long)kpad_bytes + 127) / 128 * 128;
+    if (p % 4096 == 0) p += 128;
+    return p * 256 < 0x7fffffffL ? p : kpad_bytes;         // (256 rows of it in one buffer descriptor)
+}
+
 struct MatmulGeom {
     int kpad_bytes, kchunks;
+    long pitch;                // row pitch of the copies
     bool pad_a, pad_b;
     bool gemv;                 // at most GEMV_MAX_ROWS rows: the dot-product kernel instead of the matrix units
     size_t a_bytes, b_bytes, fix_bytes, split_bytes;
 };
 
-int matmul_geom(int m, int n, int k, long lda, long ldb, int dtype, MatmulGeom *g)
+// narrow: copies of operands without padding between the rows (a workspace that holds no more)
+int matmul_geom(int m, int n, int k, long lda, long ldb, int dtype, MatmulGeom *g, bool narrow = false)
 {
     if (!dtype_ok(dtype)) return UNIT_EINVAL;
     if (m <= 0 || n <= 0 || k <= 0 || lda < k || ldb < k) return UNIT_EINVAL;
@@ -467,8 +479,9 @@ int matmul_geom(int m, int n, int k, long lda, long ldb, int dtype, MatmulGeom *
     bool ktail = ((long)k * es) % 16 != 0;
     g->pad_a = ktail || (lda * es) % 16 != 0;
     g->pad_b = ktail || (ldb * es) % 16 != 0;
-    g->a_bytes = g->pad_a ? align256((size_t)m * g->kpad_bytes) : 0;
-    g->b_bytes = g->pad_b ? align256((size_t)n * g->kpad_bytes) : 0;
+    g->pitch = narrow ? g->kpad_bytes : copy_pitch(g->kpad_bytes);
+    g->a_bytes = g->pad_a ? align256((size_t)m * g->pitch) : 0;
+    g->b_bytes = g->pad_b ? align256((size_t)n * g->pitch) : 0;
     g->fix_bytes = dtype == UNIT_U8I8 ? align256((size_t)n * 4) : 0;
     g->gemv = m <= GEMV_MAX_ROWS && (dtype == UNIT_I8 || dtype == UNIT_F16) && !tile_is_forced();
     TileChoice ch = select_tile(m, n, g->kchunks, dtype, BSRC_PLAIN);
@@ -488,6 +501,10 @@ int matmul_any(int dtype, int m, int n, int k, const void *A, long lda, const vo
     if ((!g.pad_a && !aligned16(A)) || (!g.pad_b && !aligned16(B))) return UNIT_EINVAL;
     if (reinterpret_cast<uintptr_t>(C) & 3) return UNIT_EINVAL;
     size_t need = g.a_bytes + g.b_bytes + g.fix_bytes + g.split_bytes;
+    if (ws_bytes < need && (g.pad_a || g.pad_b)) {
+        matmul_geom(m, n, k, lda, ldb, dtype, &g, true);
+        need = g.a_bytes + g.b_bytes + g.fix_bytes + g.split_bytes;
+    }
     if (need && (!ws || ws_bytes < need)) return UNIT_EWORKSPACE;
     if (need && !aligned256(ws)) return UNIT_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -498,12 +515,12 @@ int matmul_any(int dtype, int m, int n, int k, const void *A, long lda, const vo
     PadRows pad[2];
     int npad = 0;
     if (g.pad_a) {
-        pad[npad++] = {Ap, lda_b, wsp, m};
-        Ap = wsp;  lda_b = g.kpad_bytes;  wsp += g.a_bytes;
+        pad[npad++] = {Ap, lda_b, wsp, g.pitch, m};
+        Ap = wsp;  lda_b = g.pitch;  wsp += g.a_bytes;
     }
     if (g.pad_b) {
-        pad[npad++] = {Bp, ldb_b, wsp, n};
-        Bp = wsp;  ldb_b = g.kpad_bytes;  wsp += g.b_bytes;
+        pad[npad++] = {Bp, ldb_b, wsp, g.pitch, n};
+        Bp = wsp;  ldb_b = g.pitch;  wsp += g.b_bytes;
     }
     if (npad) UNIT_HIP(launch_pad_rows(pad, npad, k * es, g.kchunks, st));
     if (g.gemv) {

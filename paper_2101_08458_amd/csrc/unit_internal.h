@@ -59,7 +59,7 @@ struct PackActs { const void *x;  void *xp;  int n, c, h, w, sh, sw, p, q; };
 hipError_t launch_pack(int dtype, const PackWeights *w, const PackActs *x, hipStream_t st);
 hipError_t launch_unpack_act_i8(int n, int c, int h, int w, const void *xp, int8_t *x, hipStream_t st);
 // one operand of launch_pad_rows
-struct PadRows { const uint8_t *src; long ld_bytes; uint8_t *dst; int rows; };
+struct PadRows { const uint8_t *src; long ld_bytes; uint8_t *dst; long dst_ld; int rows; };
 hipError_t launch_pad_rows(const PadRows *ops, int nops, int row_bytes, int row_chunks, hipStream_t st);
 
 // out[r] = 128 * sum of the signed bytes of row r (rows 16-byte aligned, chunks*16 bytes long)
