@@ -47,7 +47,8 @@ bool tile_fits(int tile, int dtype, int bsrc)
     const TileCfg &c = (dtype == 4 /* fp8 */ ? g_tiles_fp8 : g_tiles)[tile];
     if (c.bm == 0) return false;                                     // no kernel of this tile for the type
     if (tile == TILE_DEEP && bsrc != BSRC_PLAIN) return false;       // ... nor for conv input (tiles.def)
-    if (tile >= TILE_QUAD && ((bsrc != BSRC_PLAIN && bsrc != BSRC_GATHER) || dtype > 2)) return false;     // (int8, fp16, bf16)
+    if (tile == TILE_STREAM && bsrc != BSRC_PLAIN) return false;
+    if (tile >= TILE_QUAD && tile < TILE_STREAM && ((bsrc != BSRC_PLAIN && bsrc != BSRC_GATHER) || dtype > 2)) return false;     // (int8, fp16, bf16)
     const int nw = c.wgm * c.wgn * c.wgk, rpi = 1024 / c.bkb;
     const int lpt = c.bm / rpi / nw + c.bn / rpi / nw;
     const long edge = (bsrc == BSRC_NCHWS || bsrc == BSRC_NCHW) ? 1024 : 0;   // (NCHW may become NCHWE)
@@ -131,6 +132,20 @@ TileChoice select_tile(int rows, int cols, int kchunks, int dtype, int bsrc, boo
                                         (bsrc != BSRC_NCHWS || (cb > 0 && cb % 16 == 0)));
         if (pick && tile_fits(12, dtype, bsrc)) tile = 12;
     }
+    // Few rows against a weight matrix that 16x16 tiles cover in at most 512 workgroups: the 16x16 tile also for 16 rows and
+    // fewer (four times the workgroups of 16x64, and no split of the reduction: 16x4096x1024 fp16 4.0 -> 3.2 us, 8x1000x3072 int8
+    // 5.5 -> 3.4, 8x8192x512 bf16 3.6 -> 3.2; beyond 512 it loses, 16x16384x1024 fp16 5.4 against 6.3), and from 384 chunks on
+    // its form with 512-byte steps, twice the bytes in flight per unit (16x4096x4096 bf16 8.9 -> 7.1 us, 32x2048x8192 14.6 ->
+    // 10.3, 17x4000x8000 int8 8.8 -> 8.1, weights beyond the caches 13.5 -> 11.3; at 256 chunks 5 to 20 % slower).  Up to 16
+    // rows a deep reduction over few tiles stays split across workgroups (12x600x8192 fp16, weights beyond the caches: 10.4
+    // us against 13.0), and 1024 chunks and more keep the split of the 16x16 tile.
+    const long n16 = (long)cdiv(rows, 16) * cdiv(cols, 16);
+    if (bsrc == BSRC_PLAIN && n16 <= 2 * CUS && tile_fits(TILE_STREAM, dtype, bsrc)) {
+        const bool deep = kchunks >= 384 && kchunks < 1024;
+        if (tile == 12 && deep) tile = TILE_STREAM;
+        if (tile == 5 && kchunks < 384) tile = 12;
+        if (tile == 5 && deep && (kchunks <= 512 || n16 >= CUS)) tile = TILE_STREAM;
+    }
     // Plain products of more than one round of 64x64 tiles (two workgroups to a compute unit: 512) and at most one
     // 128x128 tile per compute unit: nothing else would run beside that tile, so it takes the LDS of four stages.
     // 1536x1536 and 2048x2048, reduction 2048 (fp16 / int8 / fp8): 24.4 / 13.8 / 13.7 us on 64x64 -> 19.1 / 12.3 / 11.8,
@@ -177,6 +192,8 @@ TileChoice select_tile(int rows, int cols, int kchunks, int dtype, int bsrc, boo
         // the 16x16 tile exists to avoid the reduce launch: measured best unsplit up to 20 of its steps (Table I layer 1
         // in fp16, the 512-channel 3x3 layers); only far deeper reductions are cut, into slices of 32 steps
         if (ksteps_tile >= 64) split = ksteps_tile / 32;
+    } else if (tile == TILE_STREAM) {
+        // (the same: its rule ends below the depth that is cut)
     } else if (ksteps >= 24 && nt <= CUS / 2) {
         split = ksteps / 6;
         int cap = (int)(2 * CUS / nt);

@@ -18,7 +18,7 @@ struct TileCfg {
     int nst;                  // LDS stages
 };
 // TILE_QUAD and the two after it: large tiles on four waves (IgemmCfg::QUAD)
-enum { NUM_TILES = 17, TILE_DEEP = 13, TILE_QUAD = 14 };
+enum { NUM_TILES = 18, TILE_DEEP = 13, TILE_QUAD = 14, TILE_STREAM = 17 };
 extern const TileCfg g_tiles[NUM_TILES];
 extern const TileCfg g_tiles_fp8[NUM_TILES];   // same tiles, wave grids of the fp8 kernels
 
