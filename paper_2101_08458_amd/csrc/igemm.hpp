@@ -544,7 +544,7 @@ igemm_kernel(const IgemmArgs g)
                         return ((1u << hi) - 1u) & ~((1u << lo) - 1u);
                     };
                     unsigned rows = bits(bh, g.H, g.R);
-                    if (g.T > 1 || g.D > 1) {
+                    if (g.T > 1 || g.D > 1 || g.pd > 0) {       // (one plane and one tap plane: padding in depth makes whole output planes zero)
                         const int lo = bd < 0 ? (-bd < g.T ? -bd : g.T) : 0, left = g.D - bd;
                         const int hi = left < g.T ? (left < 0 ? 0 : left) : g.T;
                         rows *= g.tap_planes & ((1u << (hi * g.R)) - 1u) & ~((1u << (lo * g.R)) - 1u);

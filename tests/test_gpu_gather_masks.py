@@ -34,3 +34,21 @@ def test_taps_at_the_border(c, dims, win, stride, pad):
             unit.unit_conv3d_i8(d, xd, wd, y, ws)
         torch.cuda.synchronize()
         assert same(host(y), ref, f"tile {tile} split {split}")
+
+
+# One plane of input and one tap plane, with padding in depth: the output planes beside the middle one lie wholly in the padding and
+# are zero, whatever the neighbouring images hold.
+@pytest.mark.parametrize("c,win,stride,pad", [(128, (1, 3, 3), (1, 2, 2), (1, 1, 1)), (24, (1, 3, 3), (1, 1, 1), (1, 1, 1)),
+                                              (40, (1, 1, 1), (1, 2, 2), (1, 0, 0)), (128, (1, 3, 2), (2, 1, 1), (2, 0, 1)),
+                                              (24, (1, 5, 3), (3, 2, 1), (2, 2, 1))])
+def test_depth_padding_around_one_plane(c, win, stride, pad):
+    g = wl.rng(134, c + sum(win))
+    x, w = wl.int8_activations(g, (3, c, 1, 8, 9)), wl.int8_weights(g, (20, c) + win)
+    ref = oracle.conv3d_i8(x, w, stride, pad)
+    d = unit.conv3d_desc(3, c, 1, 8, 9, 20, *win, stride, pad)
+    announce("depth padding", c, win, stride, pad)
+    ws = torch.empty(max(unit.unit_conv3d_workspace(d, unit.UNIT_I8), 256), dtype=torch.uint8, device="cuda:0")
+    y = torch.full(ref.shape, -7, dtype=torch.int32, device="cuda:0")
+    unit.unit_conv3d_i8(d, dev(x), dev(w), y, ws)
+    torch.cuda.synchronize()
+    assert same(host(y), ref, "depth padding")
