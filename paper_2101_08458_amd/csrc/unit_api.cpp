@@ -256,10 +256,10 @@ bool nchw_direct_ok(const ConvND *d, int dtype, const void *x, const unit_requan
 }
 
 // The general direct read (BSRC_NCHWS): stride 1, output grid equal to the input grid
-// ("same" padding), whole steps inside one tap, and a tile shape that has a kernel in this mode.
+// ("same" padding, none in depth), whole steps inside one tap, and a tile shape that has a kernel in this mode.
 bool nchw_shift_ok(const ConvND *d, int dtype, const ConvGeom &g, const void *x, const unit_requant *rq)
 {
-    if (rq || dtype == UNIT_U8I8 || d->d != 1 || d->t != 1) return false;
+    if (rq || dtype == UNIT_U8I8 || d->d != 1 || d->t != 1 || d->pad_d != 0) return false;
     if (d->stride_h != 1 || d->stride_w != 1) return false;
     if (2 * d->pad_h != d->r - 1 || 2 * d->pad_w != d->s - 1) return false;
     if (reinterpret_cast<uintptr_t>(x) & 15) return false;

@@ -230,6 +230,18 @@ def test_input_mode_decisions_are_host_logic(lib):
     assert direct == 46
 
 
+def test_depth_padding_is_no_shifted_read(lib):
+    """The shifted read takes the output's pixels per image for the input's, so a window that keeps height and width but adds
+    planes by padding in depth packs its activations: the call asks for their workspace (and fails before any launch)."""
+    d = lambda pad_d: unit.conv3d_desc(2, 128, 1, 28, 28, 20, 1, 3, 3, (1, 1, 1), (pad_d, 1, 1))
+    weights, acts = 20 * 9 * 128, 2 * 128 * 28 * 28
+    fake = 0x1000
+    for pad_d in (1, 2):
+        assert unit.unit_conv3d_out_dims(d(pad_d)) == (1 + 2 * pad_d, 28, 28)
+        for size in (weights, weights + acts - 1):
+            assert lib.unit_conv3d_i8(ctypes.byref(d(pad_d)), fake, fake, fake, fake, size, 0) == unit.UNIT_EWORKSPACE
+
+
 def test_debug_force_tile_overrides_and_restores_the_rule(lib):
     """The sweep / test hook is a setter, not an environment variable: what it forces shows up in the
     selector queries, a tile without a kernel for an input mode falls back to packed activations,

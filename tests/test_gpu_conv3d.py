@@ -69,3 +69,25 @@ def test_conv3d_depth_one_matches_conv2d_call():
     torch.cuda.synchronize()
     assert same(host(y3)[:, :, 0], host(y2), "depth 1")
     assert same(host(y2), oracle.conv2d_i8(x, w, (2, 2), (1, 1)), "vs oracle")
+
+
+# n, c, window, pad: layers of one plane that would be read directly, shifted, if there were no padding in depth
+@pytest.mark.parametrize("n,c,win,pad", [(1, 128, (1, 3, 3), (1, 1, 1)), (2, 128, (1, 3, 3), (2, 1, 1)), (2, 128, (1, 1, 1), (1, 0, 0)),
+                                         (3, 256, (1, 5, 3), (1, 2, 1))])
+def test_depth_padding_of_one_plane_keeps_height_and_width(n, c, win, pad):
+    g = wl.rng(135, c + n)
+    x, w = wl.int8_activations(g, (n, c, 1, 9, 10)), wl.int8_weights(g, (24, c) + win)
+    ref = oracle.conv3d_i8(x, w, (1, 1, 1), pad)
+    desc = unit.conv3d_desc(n, c, 1, 9, 10, 24, *win, (1, 1, 1), pad)
+    y = torch.full(ref.shape, -7, dtype=torch.int32, device="cuda:0")
+    announce("conv3d, depth padding of one plane", n, c, win, pad)
+    unit.unit_conv3d_i8(desc, dev(x), dev(w), y, ws(unit.unit_conv3d_workspace(desc, unit.UNIT_I8)))
+    torch.cuda.synchronize()
+    assert same(host(y), ref, "int8")
+    xh, wh = wl.f16_activations(g, (n, c, 1, 9, 10)), wl.f16_weights(g, (24, c) + win, c * win[1] * win[2])
+    refh, truth, mag = oracle.conv3d_f16(xh, wh, (1, 1, 1), pad)
+    yf = torch.full(ref.shape, -7.0, dtype=torch.float32, device="cuda:0")
+    unit.unit_conv3d_f16(desc, dev(xh), dev(wh), yf, ws(unit.unit_conv3d_workspace(desc, unit.UNIT_F16)))
+    torch.cuda.synchronize()
+    got = host(yf).astype(np.float64)
+    assert (np.abs(got - truth) <= c * win[1] * win[2] * 2.0 ** -24 * mag + 1e-30).all()
