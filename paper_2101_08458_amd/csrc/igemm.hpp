@@ -17,6 +17,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace unit {
 
 typedef int      v4i  __attribute__((ext_vector_type(4)));
@@ -38,7 +40,8 @@ typedef __bf16   v8bf __attribute__((ext_vector_type(8)));
 // conv padding the correction sums every tap, so both cancel exactly.
 // DT_FP8 (OCP E4M3) uses the 32-byte-per-lane MFMAs: its fragments are two 16-byte chunks wide.
 enum { DT_I8 = 0, DT_F16 = 1, DT_BF16 = 2, DT_U8A = 3, DT_U8B = 4, DT_FP8 = 5 };
-enum { EPI_RAW = 0, EPI_REQUANT = 1 };
+// EPI_RAW_CHAINS: raw sums, float ones in short chains (picked by the launcher, see CHAINS)
+enum { EPI_RAW = 0, EPI_REQUANT = 1, EPI_RAW_CHAINS = 2 };
 // where the B operand (columns) comes from: a plain matrix, the packed-NHWC conv gather, or
 // an NCHW tensor read directly (1x1 stride-1 unpadded convs: channel rows of pixels,
 // transposed on the way from LDS into the fragments).  BSRC_NCHWS is the general form of the
@@ -880,6 +883,28 @@ igemm_kernel(const IgemmArgs g)
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int e = 0; e < M::NACC; ++e) acc[i][j][e] = 0;
+    // Deep reductions of few rows run unsplit on the 16x16 tiles.  For their float sums a chain per stage of the ring, folded into
+    // one total after three rounds of it: no chain is longer than those of a reduction split across workgroups.  (Error
+    // against 64 bits, 16x4096 fp16, reductions 2048 / 2560 / 4096 / 8000, in 1e-8: 9.6 / 9.8 / 10.3 / 12.5 split on 16x64
+    // tiles, 15.1 / 16.7 / 15.6 / 20.9 in one chain, 8.7 / 8.8 / 9.2 / 9.7 as here.  The 80 instructions cost 0.1 to 0.2 us a
+    // call, nearly all of it start-up, so only these calls have them: 16x1000x2048 fp16 5.55 us split, 3.40 in one chain, 3.61
+    // here; 16x4096x4096 bf16 8.88, 6.55, 6.63.)
+    constexpr bool CHAINS = EPI == EPI_RAW_CHAINS;
+    static_assert(!CHAINS || (TM * TN == 1 && std::is_same<elem_t, float>::value), "one accumulator of float sums");
+    acc_t chain[CHAINS ? 3 : 1], total;
+    auto clear_chains = [&]() {
+#pragma unroll
+        for (int e = 0; e < M::NACC; ++e) {
+            acc[0][0][e] = 0;
+#pragma unroll
+            for (int t = 0; t < (CHAINS ? 3 : 1); ++t) chain[t][e] = 0;
+        }
+    };
+    auto sum_of_chains = [&]() { return (acc[0][0] + chain[0]) + (chain[CHAINS ? 1 : 0] + chain[CHAINS ? 2 : 0]); };
+    if constexpr (CHAINS) {
+        clear_chains();
+        total = acc[0][0];
+    }
 
     // ---- main loop.  NST LDS stages hold the tile being multiplied and the NST-1 tiles
     // after it, which stream in by DMA while the MFMAs run.  Per step a wave runs NS
@@ -1174,6 +1199,7 @@ igemm_kernel(const IgemmArgs g)
                 constexpr int STG = decltype(stage_c)::value;
                 constexpr int next_stage = (STG + 1) % NST;
                 constexpr int prev_stage = (STG + NST - 1) % NST;
+                constexpr bool OWN = CHAINS && STG > 0;
                 issue_begin();
 #ifdef UNIT_PROBE
                 const unsigned unit_c0 = UNIT_CYC();
@@ -1205,7 +1231,7 @@ igemm_kernel(const IgemmArgs g)
                     for (int i = 0; i < TM; ++i)
 #pragma unroll
                         for (int j = 0; j < TN; ++j)
-                            M::run(acc[i][j], fa[SET * NS + s2][i], fb[SET * NS + s2][j]);
+                            M::run(OWN ? chain[OWN ? STG - 1 : 0] : acc[i][j], fa[SET * NS + s2][i], fb[SET * NS + s2][j]);
                 {
                     // the reads go first (their data is due one step later), then the DMAs are
                     // spread between the MFMAs
@@ -1222,8 +1248,15 @@ igemm_kernel(const IgemmArgs g)
             };
             // (whole rounds of the ring in a loop with a single exit, then the remaining steps: a loop with an
             // exit after every step makes the compiler carry an exit flag and placeholder copies through each step)
-            int steps_left = ks_end - ks_begin;
+            int steps_left = ks_end - ks_begin, rounds = 0;
             for (; steps_left >= 4; steps_left -= 4) {
+                if constexpr (CHAINS) {
+                    if (rounds++ == 3) {
+                        total += sum_of_chains();
+                        clear_chains();
+                        rounds = 1;
+                    }
+                }
                 whole_step(IntC<0>{}, IntC<0>{});
                 whole_step(IntC<1>{}, IntC<1>{});
                 whole_step(IntC<0>{}, IntC<2>{});
@@ -1232,6 +1265,7 @@ igemm_kernel(const IgemmArgs g)
             if (steps_left >= 1) whole_step(IntC<0>{}, IntC<0>{});
             if (steps_left >= 2) whole_step(IntC<1>{}, IntC<1>{});
             if (steps_left >= 3) whole_step(IntC<0>{}, IntC<2>{});
+            if constexpr (CHAINS) acc[0][0] = total + sum_of_chains();
         } else {
         read_frags(0, 0, 0);
         for (int ks = ks_begin; ks < ks_end; ++ks) {
@@ -1468,8 +1502,19 @@ igemm_kernel(const IgemmArgs g)
             if (WGK > 1) {
                 const int gidx = q * WGK + wk;
                 v4e v = red[((0 * WGM * WGN + wmn) * NG + gidx) * 64 + lane];
+                if constexpr (CHAINS) {                 // (in pairs: fewer roundings on the way of each wave's sum)
+                    v4e part[WGK];
 #pragma unroll
-                for (int k2 = 1; k2 < WGK; ++k2) v += red[((k2 * WGM * WGN + wmn) * NG + gidx) * 64 + lane];
+                    for (int k2 = 0; k2 < WGK; ++k2) part[k2] = red[((k2 * WGM * WGN + wmn) * NG + gidx) * 64 + lane];
+#pragma unroll
+                    for (int d = 1; d < WGK; d *= 2)
+#pragma unroll
+                        for (int k2 = 0; k2 + d < WGK; k2 += 2 * d) part[k2] += part[k2 + d];
+                    v = part[0];
+                } else {
+#pragma unroll
+                    for (int k2 = 1; k2 < WGK; ++k2) v += red[((k2 * WGM * WGN + wmn) * NG + gidx) * 64 + lane];
+                }
                 val[q] = v;
             } else {
                 // (u and q are unrolled constants here, so this indexes registers statically)
@@ -1477,7 +1522,7 @@ igemm_kernel(const IgemmArgs g)
                              acc[u / TN][u % TN][4 * q + 2], acc[u / TN][u % TN][4 * q + 3]};
             }
         }
-        if (EPI == EPI_RAW) {
+        if (EPI != EPI_REQUANT) {
             // 4-byte stores through a buffer descriptor anchored at the tile's first row; out-of-tile
             // lanes get an out-of-range offset and are dropped by the hardware.  Unsigned operands: per
             // column (DT_U8A) one correction for the group, per row (DT_U8B) one 16-byte load of four.
