@@ -55,3 +55,29 @@ def test_plain_calls(n, c, h, w_, k, win, stride, pad):
             fn(d, dev(x), dev(w), y, ws)
         torch.cuda.synchronize()
         assert same(host(y), ref.numpy().astype(np.int32), f"type {ut}")
+
+
+# Many output channels of few chunks: several to a workgroup, and the last workgroup partly empty.
+@pytest.mark.parametrize("k,c,r", [(100003, 16, 1), (4099, 5, 3), (2051, 33, 1)])
+@pytest.mark.parametrize("dtype", ["i8", "f16"])
+def test_packed_weights_of_many_channels(dtype, k, c, r):
+    test_packed_weights_bytes(dtype, k, c, r)
+
+
+# Unsigned activations: more output channels than the launch has workgroups for weights (2^20), and images whose packing takes more
+# workgroups than a flat grid holds (2^24), so that weights and activations are packed in a launch each.
+@pytest.mark.parametrize("n,c,k", [(1, 9, (1 << 20) + 5), (65535, 64 * 256 + 5, 3)])
+def test_plain_calls_of_very_many_workgroups(n, c, k):
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(n + c)
+    w = torch.randint(-128, 128, (k, c, 1, 1), generator=g, device="cuda:0", dtype=torch.int8)
+    x = torch.randint(0, 256, (n, c, 1, 1), generator=g, device="cuda:0", dtype=torch.uint8)
+    d = unit.conv_desc(n, c, 1, 1, k, 1, 1)
+    y = torch.full((n, k, 1, 1), -7, dtype=torch.int32, device="cuda:0")
+    ws = scratch(unit.unit_conv2d_workspace(d, unit.UNIT_U8I8))
+    announce("plain conv, many workgroups", n, c, k)
+    unit.unit_conv2d_u8i8(d, x, w, y, ws)
+    torch.cuda.synchronize()
+    wd = w.view(k, c).double()
+    ref = torch.cat([part.double() @ wd.t() for part in x.view(n, c).split(8192)])
+    assert torch.equal(y.view(n, k), ref.to(torch.int32))
