@@ -228,7 +228,8 @@ __device__ __forceinline__ void pack_weights_block(const PackW &a, int blk, int 
 // by their launch on all but large layers, and a call with plain operands needs both before its main kernel: one launch
 // instead of two, or three with the weights' sums (3x3, 128 channels, 28x28, batch 8, u8 x i8, whole call: 15.2 -> 10.1 us;
 // 3x3x3, 128 channels, 4x28x28, fp16: 17.9 -> 16.0).
-enum { ACT_TR = 0, ACT_TILE = 1, ACT_SMALL = 2 };
+// (ACT_SMALL + c: pixels of at most c channels, one chunk)
+enum { ACT_TR = 0, ACT_TILE = 1, ACT_SMALL = 2, ACT_SMALL4 = ACT_SMALL + 4, ACT_SMALL8 = ACT_SMALL + 8, ACT_SMALL16 = ACT_SMALL + 16 };
 struct PackA {
     const void *x;  uint8_t *xp;  int C, HW, cp, HWin, Q, srow, scol;  unsigned x_bytes;
     int gx, gy;  DivU dv_gx, dv_gy;                               // workgroups along the pixels and the channels of an image
@@ -239,16 +240,12 @@ __device__ __forceinline__ void pack_act_any(const PackA &a, int bx, int by, int
 {
     typedef typename std::conditional<ES == 1, int8_t, uint16_t>::type T;
     const T *x = static_cast<const T *>(a.x);
-    if (ACT == ACT_TR)
+    if constexpr (ACT == ACT_TR)
         pack_act_tr_block<ES, 128 / ES>(static_cast<const uint8_t *>(a.x), a.xp, a.C, a.HW, a.cp, a.x_bytes, bx, by, n);
-    else if (ACT == ACT_TILE)
+    else if constexpr (ACT == ACT_TILE)
         pack_act_block<T>(x, a.xp, a.C, a.HW, a.cp, a.HWin, a.Q, a.srow, a.scol, bx, by, n);
-    else if (a.C <= 4)
-        pack_act_smallc_block<T, 4>(x, a.xp, a.C, a.HW, a.HWin, a.Q, a.srow, a.scol, bx, n);
-    else if (a.C <= 8 || ES == 2)
-        pack_act_smallc_block<T, 8>(x, a.xp, a.C, a.HW, a.HWin, a.Q, a.srow, a.scol, bx, n);
     else
-        pack_act_smallc_block<T, 16 / ES>(x, a.xp, a.C, a.HW, a.HWin, a.Q, a.srow, a.scol, bx, n);
+        pack_act_smallc_block<T, ACT - ACT_SMALL>(x, a.xp, a.C, a.HW, a.HWin, a.Q, a.srow, a.scol, bx, n);
 }
 // (each alone: the shared launch's dependent argument loads and divisions cost 0.5 us)
 template <int ES, int ACT>
@@ -310,7 +307,7 @@ hipError_t launch_pack(int dtype, const PackWeights *w, const PackActs *x, hipSt
         const long x_bytes = (long)x->n * x->c * pa.HWin * es;
         pa.gy = (pa.cp + 63) / 64;
         if (x->c <= ch) {
-            act = ACT_SMALL;
+            act = x->c <= 4 ? ACT_SMALL4 : x->c <= 8 ? ACT_SMALL8 : ACT_SMALL16;
             pa.gx = (pa.HW + 255) / 256;
             pa.gy = 1;
         } else if (!sub && ((long)pa.HW * es) % 4 == 0 && (reinterpret_cast<uintptr_t>(x->x) & 15) == 0 && x_bytes < (1L << 31)) {
@@ -349,7 +346,9 @@ hipError_t launch_pack(int dtype, const PackWeights *w, const PackActs *x, hipSt
     auto pick = [&](auto es_c) {
         if (act == ACT_TR)        go(es_c, IntC<ACT_TR>{});
         else if (act == ACT_TILE) go(es_c, IntC<ACT_TILE>{});
-        else                      go(es_c, IntC<ACT_SMALL>{});
+        else if (act == ACT_SMALL4) go(es_c, IntC<ACT_SMALL4>{});
+        else if (act == ACT_SMALL8) go(es_c, IntC<ACT_SMALL8>{});
+        else if constexpr (decltype(es_c)::value == 1) go(es_c, IntC<ACT_SMALL16>{});
     };
     if (es == 1) pick(IntC<1>{});
     else         pick(IntC<2>{});

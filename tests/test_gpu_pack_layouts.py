@@ -57,6 +57,24 @@ def test_plain_calls(n, c, h, w_, k, win, stride, pad):
         assert same(host(y), ref.numpy().astype(np.int32), f"type {ut}")
 
 
+# Pixels of one chunk: a kernel each for up to 4, 8 and 16 channels, with and without weights in the same launch.
+@pytest.mark.parametrize("c", [1, 4, 5, 8, 9, 16])
+def test_few_channels(c):
+    test_plain_calls(2, c, 20, 18, 24, 5, 2, 2)
+    g = wl.rng(136, c)
+    for dtype, np_t, ch in (("i8", np.int8, 16), ("f16", np.uint16, 8)):
+        if c > ch:
+            continue
+        x = g.integers(np.iinfo(np_t).min, np.iinfo(np_t).max + 1, (3, c, 19, 23)).astype(np_t)
+        exp = np.zeros((3, 19, 23, ch), np_t)
+        exp[..., :c] = x.transpose(0, 2, 3, 1)
+        xp = scratch((exp.nbytes + 255) // 256 * 256)
+        announce("pack activations", dtype, c)
+        (unit.unit_pack_act_i8 if dtype == "i8" else unit.unit_pack_act_f16)(3, c, 19, 23, dev(x), xp)
+        torch.cuda.synchronize()
+        assert same(host(xp).view(np_t)[:exp.size].reshape(exp.shape), exp, "packed activations")
+
+
 # Many output channels of few chunks: several to a workgroup, and the last workgroup partly empty.
 @pytest.mark.parametrize("k,c,r", [(100003, 16, 1), (4099, 5, 3), (2051, 33, 1)])
 @pytest.mark.parametrize("dtype", ["i8", "f16"])
