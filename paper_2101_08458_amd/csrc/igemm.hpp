@@ -479,8 +479,8 @@ igemm_kernel(const IgemmArgs g)
     const int lr_blk = lane / NCH;                                  // row inside a DMA block
     const int cT = (lane % NCH) ^ swz<NCH>(wave * RPI + lr_blk);    // logical chunk this thread fetches
     const int rows_here = (g.rows - row0 < BM) ? g.rows - row0 : BM;
-    const __amdgpu_buffer_rsrc_t rsA =
-        make_rsrc(g.A + (long)row0 * g.lda, (unsigned)((long)(rows_here - 1) * g.lda + (long)g.kchunks * 16));
+    const unsigned a_bytes = (unsigned)((long)(rows_here - 1) * g.lda + (long)g.kchunks * 16);
+    const __amdgpu_buffer_rsrc_t rsA = make_rsrc(g.A + (long)row0 * g.lda, a_bytes);
     unsigned offA[IA];
 #pragma unroll
     for (int j = 0; j < IA; ++j) {
@@ -632,13 +632,22 @@ igemm_kernel(const IgemmArgs g)
     if (EDGE1) rt_cb = ks_begin * NCH;  // 1x1 mode: first reduction chunk of the step being read
     int it_base = ((it_r - g.ph) * g.W + (it_s - g.pw)) * ES, it_cbo = it_cb * EPC * ES * g.PQ;
 
-    // Before the last tile of the slice, and every tile past it, is issued: the step's uniform offset moves into the lanes'
-    // own, and lanes whose chunk lies past the slice's end get one out of range (they read zeros; past the last tile those
-    // are all lanes).  A scalar branch taken a few times per workgroup; all other tiles cost no masking (8192^3 fp16 958 ->
-    // 932 us, 32x4096x4096 bf16 9.2 -> 8.9).  Not in the direct
-    // modes, whose small tiles have one or two loads a step to mask and wait for instructions at their cold start: there
-    // the branch's code at every copy of the step cost the 53 batch-1 layers 1.3 %.
-    constexpr bool FOLD = !(NCHW1 || BSRC == BSRC_NCHWS);
+    // Loads past the slice's end must return zeros (a last tile may lie past it in part, and up to NST tiles are requested
+    // that lie past it as a whole).  Three ways:
+    //  * FOLD: before the last tile of the slice, and every tile past it, is issued, the step's uniform offset moves into the
+    //    lanes' own, and lanes whose chunk lies past the end get one out of range.  A scalar branch taken a few times
+    //    per workgroup; all other tiles cost no masking (8192^3 fp16 958 -> 932 us, 32x4096x4096 bf16 9.2 -> 8.9).
+    //  * LIVE: where every tile of a slice is whole (a step holds chunks of one tap), tiles past the end get an empty buffer,
+    //    in scalar instructions alone.
+    //    (The uniform offset is zero then: it must not exceed the buffer's length, see dma16s.)
+    //  * LANES: a comparison per step and a select per load.
+    // The small tiles of the convs wait for instructions at their cold start, and the fold's code at every copy of the
+    // step costs them more than it saves (53 int8 layers at batch 1: +1.3 % in the direct reads, +0.4 % in the few gathers).
+    constexpr bool WHOLE = (TM * TN <= 4) && NST >= 3;          // (the register-prefetch loop below)
+    constexpr bool LIVE = BSRC == BSRC_NCHWS || (WHOLE && BSRC == BSRC_GATHERU);
+    constexpr bool LANES = NCHW1 || (WHOLE && (BSRC == BSRC_GATHER || BSRC == BSRC_GATHERW));
+    constexpr bool FOLD = !LIVE && !LANES;
+    const int lane_end = (kend - cT) * 16;          // LANES: this lane's chunk is loaded while the step's offset lies below it
     auto issue_begin = [&]() {
         if (!FOLD || kc0 + NCH < kend) return;
         const bool kok = kc0 + cT < kend;
@@ -656,10 +665,11 @@ igemm_kernel(const IgemmArgs g)
         if (BSRC == BSRC_GATHERU) {
             // (an offset whose tap is outside the image gets its top bit set, i.e. is out of range)
             const unsigned out = (no_row[j] << ((31 - utr) & 31)) | (no_col[j] << ((31 - us) & 31));
-            dma16(rsB, dst, (out & UNIT_OOB) | (offB[j] + utap));
+            dma16(LIVE ? make_rsrc(g.B, kc0 < kend ? (unsigned)g.b_bytes : 0u) : rsB, dst, (out & UNIT_OOB) | (offB[j] + utap));
         } else if (BSRC == BSRC_GATHER) {
             const unsigned tap = (unsigned)(((ct * g.H + cr) * g.W + cs) * g.CB + ccb) * 16u;
-            const unsigned out = (no_row[j] << ((31 - (ct * g.R + cr)) & 31)) | (no_col[j] << ((31 - cs) & 31));
+            unsigned out = (no_row[j] << ((31 - (ct * g.R + cr)) & 31)) | (no_col[j] << ((31 - cs) & 31));
+            if (LANES) out = (int)so < lane_end ? out : UNIT_OOB;
             dma16(rsB, dst, (out & UNIT_OOB) | (offB[j] + tap));
         } else if (BSRC == BSRC_GATHERW) {
             const unsigned tap = (unsigned)(((ct * g.H + cr) * g.W + cs) * g.CB + ccb) * 16u;
@@ -708,11 +718,13 @@ igemm_kernel(const IgemmArgs g)
     // issues the DMA of the next tile (the one whose first chunk is kc0) into `stage`
     auto issue_tile = [&](int stage) {
         uint8_t *dst = smem + stage * C::STAGE_BYTES + wave * 1024;
-        const bool kok = kc0 + cT < kend;
+        const bool kok = (int)so < lane_end;
+        const __amdgpu_buffer_rsrc_t rsA_step = LIVE ? make_rsrc(g.A + (long)row0 * g.lda, kc0 < kend ? a_bytes : 0u) : rsA;
+        const unsigned so_step = FOLD || kc0 < kend ? so : 0u;
 #pragma unroll
         for (int j = 0; j < IA; ++j) {
-            if (FOLD) dma16s(rsA, dst + j * NW * 1024, offA[j], so);
-            else      dma16(rsA, dst + j * NW * 1024, kok ? offA[j] + (unsigned)kc0 * 16u : UNIT_OOB);
+            if (LANES) dma16(rsA, dst + j * NW * 1024, kok ? offA[j] + so : UNIT_OOB);
+            else       dma16s(rsA_step, dst + j * NW * 1024, offA[j], so_step);
         }
         dst += BM * BKB;
         if (BSRC == BSRC_NCHWS) {
@@ -740,7 +752,7 @@ igemm_kernel(const IgemmArgs g)
         } else if (NCHW1) {
             // channel rows of this step: chan0 .. chan0 + BKB/ES; rows past the real channel
             // count or past the slice end come back as zeros
-            const int chan0 = kc0 * EPC;
+            const int chan0 = (int)(so / ES);
             const int chan_end = (kend * EPC < g.Cin) ? kend * EPC : g.Cin;
             // (edge variant: a chunk that is not wholly inside the tensor is not loaded: see read_frags)
             const unsigned lim = EDGE1 ? (unsigned)g.b_bytes : 0xffffffffu;
@@ -922,7 +934,6 @@ igemm_kernel(const IgemmArgs g)
     // reads every wave has consumed in its previous step's MFMAs), so the step's barrier needs
     // no wait on outstanding LDS reads: they complete behind the MFMAs and the DMA issue.
     constexpr bool QUAD = C::QUAD;
-    constexpr bool WHOLE = (TM * TN <= 4) && NST >= 3;      // (the register-prefetch schedule needs three LDS stages)
     constexpr int NSLOT = WHOLE ? 2 * NS : 2;
     frag_t fa[NSLOT][TM], fb[NSLOT][TN];
     // The direct modes issue their transposing reads as inline assembly (see lds_tr), except in the kernels with the
@@ -1085,12 +1096,17 @@ igemm_kernel(const IgemmArgs g)
         UNIT_STAMP(6);
         // A layer's weights usually come from beyond the L2, and every workgroup of an XCD walks the same rows at the same
         // time: three tiles in flight hide the L2's latency but not the one behind it.  So the workgroups that share a row tile
-        // first request a part of its rows each (contiguous for packed weights), which brings them all into the L2 at once; the
+        // first request a part of its rows each (contiguous for packed weights), which brings them into the L2 at once; the
         // bytes go to the stage that the first step refills, and are complete before tile 0 is (loads return in
-        // order).  53-layer fp16 set at batch 16: 800 -> 774 to 785 us.  Only for the gathers of nine steps and more on the
-        // register-prefetch loop: the direct reads stream as much from the activations, and lose (the batch-1 int8 set by 4 %), from
-        // five steps on the set takes 781 us, and the large tiles gain nothing (256 channels, 56x56, batch 32: +2 %).
-        if (WHOLE && MASKED && gridDim.z == 1 && ks_end - ks_begin > 8) {
+        // order).  Where a run walks one row tile after another that is all of its rows, as far as 32 loads per workgroup
+        // reach; in bands of row tiles, which take turns, a part of them only, and that is the better share: with all
+        // of them the 53-layer fp16 set takes 804 us at batch 16, as without any, with this part 785.
+        // Only for the gathers of nine steps and more on the register-prefetch loop: the direct reads stream as much from the
+        // activations, and lose (the batch-1 int8 set by 4 %), from five steps on the set takes 781 us, and the large tiles gain
+        // nothing (256 channels, 56x56, batch 32: +2 %).  The 16x16 tiles of a single image have few workgroups to share
+        // the rows and start cold, so there it needs more than one workgroup per unit (the sets without it on 16x16 and 32x32 tiles and
+        // with it: fp16 batch 8 612 -> 604 us, batch 4 470 -> 448, int8 batch 4 350 -> 340; with it always, batch 1: +1 us).
+        if (WHOLE && MASKED && (BM >= 32 || ntiles > 256) && gridDim.z == 1 && ks_end - ks_begin > 8) {
             const int run = ntiles >> 3;                    // workgroups of an XCD, of which tiles_n share a row tile
             const int share = run >= tiles_n ? tiles_n : run > 0 ? run : 1;
             const int loads = (rows_here * g.kchunks + 63) / 64, per = (loads + share - 1) / share;
