@@ -456,6 +456,10 @@ inline long copy_pitch(int kpad_bytes)
     if (p % 4096 == 0) p += 128;
     return p * 256 < 0x7fffffffL ? p : kpad_bytes;         // (256 rows of it in one buffer descriptor)
 }
+// ... from this many bytes a row on (0.98 to 1.05 times as fast as dense rows, 1.02 to 1.14 from 1 KiB on; int8 and fp16,
+// 64 to 8192 rows).  Shorter rows stay dense: up to half as many bytes again cost more than split lines do (32 to 400
+// bytes: lines 0.92 to 1.03 times as fast, mostly below 1; 64x8192x270 int8 8.17 us dense, 8.75 in lines).
+enum { LINE_PITCH_FROM = 512 };
 
 struct MatmulGeom {
     int kpad_bytes, kchunks;
@@ -465,7 +469,7 @@ struct MatmulGeom {
     size_t a_bytes, b_bytes, fix_bytes, split_bytes;
 };
 
-// narrow: copies of operands without padding between the rows (a workspace that holds no more)
+// narrow: copies of operands without padding between the rows (short ones, or a workspace that holds no more)
 int matmul_geom(int m, int n, int k, long lda, long ldb, int dtype, MatmulGeom *g, bool narrow = false)
 {
     if (!dtype_ok(dtype)) return UNIT_EINVAL;
@@ -501,7 +505,7 @@ int matmul_any(int dtype, int m, int n, int k, const void *A, long lda, const vo
     if ((!g.pad_a && !aligned16(A)) || (!g.pad_b && !aligned16(B))) return UNIT_EINVAL;
     if (reinterpret_cast<uintptr_t>(C) & 3) return UNIT_EINVAL;
     size_t need = g.a_bytes + g.b_bytes + g.fix_bytes + g.split_bytes;
-    if (ws_bytes < need && (g.pad_a || g.pad_b)) {
+    if ((ws_bytes < need || g.kpad_bytes < LINE_PITCH_FROM) && (g.pad_a || g.pad_b)) {
         matmul_geom(m, n, k, lda, ldb, dtype, &g, true);
         need = g.a_bytes + g.b_bytes + g.fix_bytes + g.split_bytes;
     }

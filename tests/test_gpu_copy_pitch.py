@@ -38,3 +38,10 @@ def test_both_pitches(dtype, m, n, k, lda, ldb):
         assert torch.equal(c.double(), exact)
     with pytest.raises(unit.UnitError):
         fn(m, n, k, a, lda, b, ldb, c, n, torch.empty(bare - 1, dtype=torch.uint8, device=DEV))
+
+
+# Rows around the 512 bytes from which copies have whole lines, on tiles of each size and on the one-row kernel.
+@pytest.mark.parametrize("m,n", [(2, 70), (40, 150), (600, 513), (2100, 1100)])
+@pytest.mark.parametrize("k", [13, 479, 497, 511, 513])
+def test_short_rows(k, m, n):
+    test_both_pitches("i8", m, n, k, k, k + 3)
