@@ -41,7 +41,8 @@ typedef __bf16   v8bf __attribute__((ext_vector_type(8)));
 // DT_FP8 (OCP E4M3) uses the 32-byte-per-lane MFMAs: its fragments are two 16-byte chunks wide.
 enum { DT_I8 = 0, DT_F16 = 1, DT_BF16 = 2, DT_U8A = 3, DT_U8B = 4, DT_FP8 = 5 };
 // EPI_RAW_CHAINS: raw sums, float ones in short chains (picked by the launcher, see CHAINS)
-enum { EPI_RAW = 0, EPI_REQUANT = 1, EPI_RAW_CHAINS = 2 };
+// EPI_RAW_SHORT: raw sums of few steps (picked by the launcher, see LANES)
+enum { EPI_RAW = 0, EPI_REQUANT = 1, EPI_RAW_CHAINS = 2, EPI_RAW_SHORT = 3 };
 // where the B operand (columns) comes from: a plain matrix, the packed-NHWC conv gather, or
 // an NCHW tensor read directly (1x1 stride-1 unpadded convs: channel rows of pixels,
 // transposed on the way from LDS into the fragments).  BSRC_NCHWS is the general form of the
@@ -640,12 +641,14 @@ igemm_kernel(const IgemmArgs g)
     //  * LIVE: where every tile of a slice is whole (a step holds chunks of one tap), tiles past the end get an empty buffer,
     //    in scalar instructions alone.
     //    (The uniform offset is zero then: it must not exceed the buffer's length, see dma16s.)
-    //  * LANES: a comparison per step and a select per load.
+    //  * LANES: a comparison per step and a select per load.  Also on plain rows of small tiles for at most four steps, most of which
+    //    the fold's branch would be taken in (512x512 int8, 64 / 256 / 400 bytes: 2.54 / 2.61 / 2.81 us folded, 2.44 / 2.55 /
+    //    2.73 so; from eight steps on the fold wins: 1000x600, 4096 bytes, 6.92 us against 7.25).
     // The small tiles of the convs wait for instructions at their cold start, and the fold's code at every copy of the
     // step costs them more than it saves (53 int8 layers at batch 1: +1.3 % in the direct reads, +0.4 % in the few gathers).
     constexpr bool WHOLE = (TM * TN <= 4) && NST >= 3;          // (the register-prefetch loop below)
     constexpr bool LIVE = BSRC == BSRC_NCHWS || (WHOLE && BSRC == BSRC_GATHERU);
-    constexpr bool LANES = NCHW1 || (WHOLE && (BSRC == BSRC_GATHER || BSRC == BSRC_GATHERW));
+    constexpr bool LANES = NCHW1 || (WHOLE && (BSRC == BSRC_GATHER || BSRC == BSRC_GATHERW)) || EPI == EPI_RAW_SHORT;
     constexpr bool FOLD = !LIVE && !LANES;
     const int lane_end = (kend - cT) * 16;          // LANES: this lane's chunk is loaded while the step's offset lies below it
     auto issue_begin = [&]() {
@@ -678,7 +681,8 @@ igemm_kernel(const IgemmArgs g)
                             ((unsigned)w < (unsigned)g.W);
             dma16(rsB, dst, ok ? offB[j] + tap : UNIT_OOB);
         } else {
-            dma16s(rsB, dst, offB[j], so);
+            if (LANES) dma16(rsB, dst, (int)so < lane_end ? offB[j] + so : UNIT_OOB);
+            else       dma16s(rsB, dst, offB[j], so);
         }
     };
     auto issue_next = [&]() {

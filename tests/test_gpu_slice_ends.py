@@ -40,3 +40,31 @@ def test_ends_of_the_reduction(c, win, stride, pad, tile):
         torch.cuda.synchronize()
         assert same(host(y), ref, f"int8, split {split}")
         assert ((yf[:, ::2].double() - finite).abs() <= c * win * win * 2.0 ** -24 * mag + 1e-30).all(), f"fp16, split {split}"
+
+
+# Plain rows whose pitch holds infinities behind the reduction; up to four steps and more than that are kernels of their own.
+@pytest.mark.parametrize("tile", [2, 3, 4, 5, 6, 9, 12])
+@pytest.mark.parametrize("kbytes", [16, 240, 256, 272, 496, 512, 528, 1024, 1040, 2064])
+def test_ends_of_short_products(kbytes, tile):
+    m, n, gen = 37, 300, torch.Generator(device="cuda:0")
+    gen.manual_seed(kbytes)
+    for ut, fn, tt, es in [(unit.UNIT_I8, unit.unit_matmul_i8, torch.int8, 1), (unit.UNIT_U8I8, unit.unit_matmul_u8i8, torch.int8, 1),
+                           (unit.UNIT_F16, unit.unit_matmul_f16, torch.float16, 2), (unit.UNIT_BF16, unit.unit_matmul_bf16, torch.bfloat16, 2)]:
+        k, ld = kbytes // es, kbytes // es + 32
+        if es == 1:
+            a = torch.randint(0, 256, (m, ld), generator=gen, device="cuda:0", dtype=torch.uint8)
+            a = a if ut == unit.UNIT_U8I8 else a.view(torch.int8)
+            b = torch.randint(-128, 128, (n, ld), generator=gen, device="cuda:0", dtype=torch.int8)
+        else:
+            a, b = (torch.randn((r, ld), generator=gen, device="cuda:0").to(tt) for r in (m, n))
+            a[:, k:] = b[:, k:] = float("inf")
+        exact = a[:, :k].double() @ b[:, :k].double().t()
+        mag = a[:, :k].double().abs() @ b[:, :k].double().abs().t()
+        for split in (1, 2):
+            announce("short products", ut, (m, n, k), "tile", tile, "split", split)
+            with forced(tile, split):
+                c = torch.full((m, n), -7, device="cuda:0", dtype=torch.int32 if es == 1 else torch.float32)
+                ws = torch.empty(max(unit.unit_matmul_workspace(m, n, k, ld, ld, ut), 256), dtype=torch.uint8, device="cuda:0")
+                fn(m, n, k, a, ld, b, ld, c, n, ws)
+            torch.cuda.synchronize()
+            assert ((c.double() - exact).abs() <= (0 if es == 1 else k * 2.0 ** -24) * mag).all(), (ut, split)
