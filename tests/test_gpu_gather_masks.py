@@ -1,6 +1,7 @@
 """Gather of packed activations: the tap masks at their limits (31 tap rows over all planes, 31 tap columns; wider windows take the
 kernel with a bounds test per tap), padding wider than the window, unpadded windows, planes in the padding.  Pixels of whole steps of
 channels (scalar tap walk) and of less (a tap per lane).  Integer sums, bit-exact."""
+import numpy as np
 import pytest
 import torch
 
@@ -52,3 +53,38 @@ def test_depth_padding_around_one_plane(c, win, stride, pad):
     unit.unit_conv3d_i8(d, dev(x), dev(w), y, ws)
     torch.cuda.synchronize()
     assert same(host(y), ref, "depth padding")
+
+
+# Windows too wide for the masks on the large four-wave tiles, which have no kernel for them: those calls run on the eight-wave tiles of
+# the same shapes, raw and requantised.
+@pytest.mark.parametrize("tile", [14, 15, 16])
+@pytest.mark.parametrize("c", [128, 24])
+@pytest.mark.parametrize("dims,win,pad", [((34, 9), (32, 1), (16, 0)), ((4, 36), (2, 32), (1, 16)), ((9, 8), (3, 3), (1, 1))])
+def test_wide_windows_on_large_tiles(dims, win, pad, c, tile):
+    g = wl.rng(138, c + sum(dims))
+    n, k = 3, 150
+    x, w = wl.int8_activations(g, (n, c) + dims), wl.int8_weights(g, (k, c) + win)
+    ref = oracle.conv2d_i8(x, w, (1, 1), pad)
+    scale = (127.0 / np.abs(ref).max(axis=(0, 2, 3)).clip(1)).astype(np.float32)
+    bytes_ref = oracle.requant(ref, scale, relu=False)
+    xh, wh = wl.f16_activations(g, (n, c) + dims), wl.f16_weights(g, (k, c) + win, c * win[0] * win[1])
+    d = unit.conv_desc(n, c, *dims, k, *win, 1, pad)
+    xd, wd, sd = dev(x), dev(w), dev(scale)
+    xhd, whd = dev(xh), dev(wh)
+    x64, w64 = xhd.view(torch.float16).double(), whd.view(torch.float16).double()
+    exact, mag = (torch.nn.functional.conv2d(a, b, padding=pad) for a, b in ((x64, w64), (x64.abs(), w64.abs())))
+    for split in (1, 2):
+        announce("wide windows", c, dims, win, "tile", tile, "split", split)
+        with forced(tile, split):
+            ws = torch.empty(max(unit.unit_conv2d_workspace(d, unit.UNIT_I8), unit.unit_conv2d_workspace(d, unit.UNIT_F16), 256),
+                             dtype=torch.uint8, device="cuda:0")
+            y = torch.full(ref.shape, -7, dtype=torch.int32, device="cuda:0")
+            unit.unit_conv2d_i8(d, xd, wd, y, None, None, ws)
+            y8 = torch.full(ref.shape, -7, dtype=torch.int8, device="cuda:0")
+            unit.unit_conv2d_i8(d, xd, wd, None, unit.make_requant(sd, relu=False), y8, ws)
+            yf = torch.full(ref.shape, -7.0, dtype=torch.float32, device="cuda:0")
+            unit.unit_conv2d_f16(d, xhd, whd, yf, ws)
+        torch.cuda.synchronize()
+        assert same(host(y), ref, f"raw, split {split}")
+        assert same(host(y8), bytes_ref, f"requantised, split {split}")
+        assert ((yf.double() - exact).abs() <= c * win[0] * win[1] * 2.0 ** -24 * mag + 1e-30).all(), f"fp16, split {split}"
