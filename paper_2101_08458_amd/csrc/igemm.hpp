@@ -105,6 +105,7 @@ struct IgemmArgs {
     int col_base, col_limit;
     int i8_wide;                                    // out_i8: images are whole numbers of 16-byte pieces
     unsigned tap_planes;                            // bit t * R for every tap plane t (masked gathers, T > 1)
+    DivU dv_share;                                  // workgroups that share the request of a row tile's weights; d = 0: none
 #ifdef UNIT_PROBE
     // instrumented build only (make probe): per wave 16 x 8 bytes of time stamps, see UNIT_STAMP
     unsigned long long *probe;
@@ -1109,13 +1110,15 @@ igemm_kernel(const IgemmArgs g)
         // activations, and lose (the batch-1 int8 set by 4 %), from five steps on the set takes 781 us, and the large tiles gain
         // nothing (256 channels, 56x56, batch 32: +2 %).  The 16x16 tiles of a single image have few workgroups to share
         // the rows and start cold, so there it needs more than one workgroup per unit (the sets without it on 16x16 and 32x32 tiles and
-        // with it: fp16 batch 8 612 -> 604 us, batch 4 470 -> 448, int8 batch 4 350 -> 340; with it always, batch 1: +1 us).
-        if (WHOLE && MASKED && (BM >= 32 || ntiles > 256) && gridDim.z == 1 && ks_end - ks_begin > 8) {
-            const int run = ntiles >> 3;                    // workgroups of an XCD, of which tiles_n share a row tile
-            const int share = run >= tiles_n ? tiles_n : run > 0 ? run : 1;
-            const int loads = (rows_here * g.kchunks + 63) / 64, per = (loads + share - 1) / share;
-            const int first = ((int)blockIdx.x >> 3) % share * per;
+        // with it: fp16 batch 8 612 -> 601 us, batch 4 466 -> 425, int8 batch 8 489 -> 471).
+        // (Which calls do is the launcher's decision, and it brings the divisor: what stands here is in the way of every cold start.
+        // 53 int8 layers at batch 1 265.5 -> 262.1 us, fp16 at batch 16 787 -> 769.)
+        if (WHOLE && MASKED && g.dv_share.d != 0) {
+            const int share = (int)g.dv_share.d, loads = (rows_here * g.kchunks + 63) / 64;
+            const int per = divu(loads + share - 1, g.dv_share), pos = (int)blockIdx.x >> 3;
+            const int first = (pos - divu(pos, g.dv_share) * share) * per;
             const int count = per < 32 ? per : 32;          // (a few loads per wave: they wait in front of tile 0)
+#pragma nounroll
             for (int b = wave; b < count; b += NW)
                 dma16(rsA, smem + (NST - 1) * C::STAGE_BYTES + wave * 1024, (unsigned)(first + b) * 1024u + (unsigned)lane * 16u);
         }
