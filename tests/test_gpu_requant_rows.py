@@ -115,3 +115,30 @@ def test_requant_scale_and_bias_are_slices(k):
             p = host(yp)
             assert same(p[:exp_packed.size].reshape(exp_packed.shape), exp_packed, f"packed, tile {tile}")
             assert (p[exp_packed.size:] == 99).all(), f"tile {tile}: written outside"
+
+
+# The four-wave tiles hand requantised results of short reductions to the eight-wave ones: reductions on both sides of the line (144 chunks
+# of 16 bytes for layers of one round of workgroups), channels of whole steps and of less, bytes in both layouts.
+@pytest.mark.parametrize("tile", [14, 15, 16])
+@pytest.mark.parametrize("c", [240, 256, 272])
+def test_requant_on_large_tiles_around_the_line(c, tile):
+    n, h, w_, k = 2, 11, 13, 270
+    g = wl.rng(139, c)
+    x, wt = wl.int8_activations(g, (n, c, h, w_)), wl.int8_weights(g, (k, c, 3, 3))
+    acc = oracle.conv2d_i8(x, wt, (1, 1), (1, 1))
+    bias = g.integers(-9000, 9000, k).astype(np.int32)
+    scale = (127.0 / np.abs(acc).max(axis=(0, 2, 3)).clip(1)).astype(np.float32)
+    exp = oracle.requant(acc, scale, bias=bias, relu=True)
+    d = unit.conv_desc(n, c, h, w_, k, 3, 3, 1, 1)
+    xd, wd, sd, bd = dev(x), dev(wt), dev(scale), dev(bias)
+    wp = torch.empty(unit.unit_packed_weights_bytes(d, unit.UNIT_I8), dtype=torch.uint8, device="cuda:0")
+    unit.unit_pack_weights_i8(d, wd, wp)
+    rq = unit.make_requant(sd, bd, relu=True)
+    with forced(tile, 1):
+        ws = torch.empty(max(unit.unit_conv2d_wpacked_workspace(d, unit.UNIT_I8), 256), dtype=torch.uint8, device="cuda:0")
+        raw = torch.full(acc.shape, -7, dtype=torch.int32, device="cuda:0")
+        y8 = torch.full(exp.shape, -7, dtype=torch.int8, device="cuda:0")
+        announce("requant around the line", c, "tile", tile)
+        unit.unit_conv2d_wpacked_i8(d, xd, wp, raw, rq, y8, ws)
+        torch.cuda.synchronize()
+    assert same(host(raw), acc, "raw") and same(host(y8), exp, "bytes")
