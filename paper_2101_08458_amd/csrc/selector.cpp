@@ -139,6 +139,9 @@ TileChoice select_tile(int rows, int cols, int kchunks, int dtype, int bsrc, boo
     // 10.3, 17x4000x8000 int8 8.8 -> 8.1, weights beyond the caches 13.5 -> 11.3; at 256 chunks 5 to 20 % slower).  Up to 16
     // rows a deep reduction over few tiles stays split across workgroups (12x600x8192 fp16, weights beyond the caches: 10.4
     // us against 13.0), and 1024 chunks and more keep the split of the 16x16 tile.
+    // (the 512-byte form beyond 512 tiles, weights beyond the caches, tile 12 / 17: 32x3840x6400 int8, 480 tiles, 11.4 / 11.5 us, 520 tiles
+    // 12.1 / 13.7, 768 tiles 16.1 / 19.2.  Within its rule and with such weights it takes 0.72 to 1.02 of tile 12's time at 17 to 48 rows; on
+    // weights that stay in the L2, one product repeated, up to 1.15: 32x4096x6144 int8 5.3 / 6.0 us.)
     const long n16 = (long)cdiv(rows, 16) * cdiv(cols, 16);
     if (bsrc == BSRC_PLAIN && n16 <= 2 * CUS && tile_fits(TILE_STREAM, dtype, bsrc)) {
         const bool deep = kchunks >= 384 && kchunks < 1024;
@@ -221,7 +224,8 @@ TileChoice select_tile(int rows, int cols, int kchunks, int dtype, int bsrc, boo
 
 // Relative cost of one tile of the narrower relatives of the 256 x 256 tile, per unit of reduction, in units of the
 // large tile's own cost (measured on matmuls that fill exactly one round of 256 workgroups with each shape).
-// (tile: next to tile 8; quad: next to TILE_QUAD)
+// (tile: next to tile 8; quad: next to TILE_QUAD, whose relatives cost the same: fp16, reductions 1024 / 4096, 0.80 / 0.78 and 0.60 /
+// 0.57; int8 0.79 / 0.79 and 0.61 / 0.58)
 static const struct { int tile, quad, bn; double cost; } g_tail_tiles[] = {{10, TILE_QUAD + 1, 192, 0.79}, {11, TILE_QUAD + 2, 128, 0.60}};
 
 RangePlan plan_ranges(int rows, int cols, int kchunks, int dtype, int bsrc, bool allow_split, int cb, bool allow_ranges)
