@@ -96,8 +96,11 @@ def late_writes(code):
 
 def main(paths):
     late, checked = [], 0
-    for p in paths if os.path.exists(OBJDUMP) else []:
-        for args, code in disassembled(p[:-len(".res")] + ".o"):
+    for p in paths:
+        obj = os.path.splitext(p)[0] + ".o"
+        if not (os.path.exists(OBJDUMP) and os.path.exists(obj)):
+            continue
+        for args, code in disassembled(obj):
             checked += 1
             late += [(p, args, w) for w in [late_writes(code)] if w]
     bad, quad, seen, spilled_builtin = [], [], 0, 0
