@@ -42,7 +42,8 @@ typedef __bf16   v8bf __attribute__((ext_vector_type(8)));
 enum { DT_I8 = 0, DT_F16 = 1, DT_BF16 = 2, DT_U8A = 3, DT_U8B = 4, DT_FP8 = 5 };
 // EPI_RAW_CHAINS: raw sums, float ones in short chains (picked by the launcher, see CHAINS)
 // EPI_RAW_SHORT: raw sums of few steps (picked by the launcher, see LANES)
-enum { EPI_RAW = 0, EPI_REQUANT = 1, EPI_RAW_CHAINS = 2, EPI_RAW_SHORT = 3 };
+// EPI_RAW_STREAM: raw sums of a conv, stored without staying in the L2 (picked by the launcher, see streams_out)
+enum { EPI_RAW = 0, EPI_REQUANT = 1, EPI_RAW_CHAINS = 2, EPI_RAW_SHORT = 3, EPI_RAW_STREAM = 4 };
 // where the B operand (columns) comes from: a plain matrix, the packed-NHWC conv gather, or
 // an NCHW tensor read directly (1x1 stride-1 unpadded convs: channel rows of pixels,
 // transposed on the way from LDS into the fragments).  BSRC_NCHWS is the general form of the
@@ -1401,8 +1402,9 @@ igemm_kernel(const IgemmArgs g)
     const __amdgpu_buffer_rsrc_t rsFix = make_rsrc(
         g.bias, !(g.bias && blockIdx.z == 0) ? 0u : (DT == DT_U8B) ? (unsigned)((g.rows * 4 + 255) & ~255) : UNIT_OOB);
     elem_t *out = reinterpret_cast<elem_t *>(g.out);
+    constexpr int OUT_AUX = EPI == EPI_RAW_STREAM ? 2 : 0;      // (2: non-temporal)
 
-    if constexpr (QUAD && EPI == EPI_RAW) {
+    if constexpr (QUAD && EPI != EPI_REQUANT) {
         // A lane's stores differ by uniform amounts: one offset per column tile in vector registers (out of range for
         // columns past the end), the row's part added by the store, and a row's columns one after another, which fill whole
         // lines.  (An address per store, one MFMA tile after another: 12 us for 256 x 256 words at 8192^3; 5.9, and
@@ -1427,7 +1429,7 @@ igemm_kernel(const IgemmArgs g)
 #pragma unroll
                     for (int j = 0; j < TN; ++j)
                         __builtin_amdgcn_raw_buffer_store_b32(to_bits(acc[i][j][e]), rsO, in ? coff[j] : UNIT_OOB,
-                                                              (unsigned)row * (unsigned)g.row_stride * 4u, 0);
+                                                              (unsigned)row * (unsigned)g.row_stride * 4u, OUT_AUX);
                 }
         };
         if (rows_here == BM) store_window(IntC<1>{});
@@ -1571,7 +1573,7 @@ igemm_kernel(const IgemmArgs g)
                     const unsigned off = ok ? (cb + (unsigned)lr * (unsigned)g.row_stride) * 4u : UNIT_OOB;
                     elem_t v = val[q][b];
                     if (DT == DT_U8A || DT == DT_U8B) v += (elem_t)fix[q][b];
-                    __builtin_amdgcn_raw_buffer_store_b32(to_bits(v), rsO, off, 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b32(to_bits(v), rsO, off, 0, OUT_AUX);
                 }
             }
         } else {
