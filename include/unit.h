@@ -259,8 +259,9 @@ int unit_conv2d_packed_f16(const unit_conv2d_desc *d, const void *x_packed, cons
 /*
  * conv2d on plain NCHW activations with pre-packed weights: the per-layer call of an
  * inference loop whose weights were packed once.  Activations are packed into the workspace
- * first, except where the main kernel can read NCHW itself (16-byte aligned x, no requantise;
- * see unit_conv2d_input_mode): 1x1 / stride-1 / unpadded convs of any batch and image size, and
+ * first, except where a kernel can read NCHW itself: layers of at most four input channels whose
+ * window fits on chip (reported as UNIT_INPUT_PACKED: they need the same workspace), and (16-byte aligned x, no requantise;
+ * see unit_conv2d_input_mode) 1x1 / stride-1 / unpadded convs of any batch and image size, and
  * small stride-1 "same"-padded convs (one image, or a few small ones).  Outputs as in unit_conv2d_i8 /
  * unit_conv2d_f16.
  */

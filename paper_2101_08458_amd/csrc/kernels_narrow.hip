@@ -1,0 +1,435 @@
+// Convs whose input pixels hold at most four channels (the first layer of a network): the implicit GEMM on pixels of four
+// channels, held in LDS.
+//
+// The general kernel's reduction walks 16-byte pixels, of which such a layer fills 3 of 16 (int8) or 6 of 16 (fp16) bytes: a 7x7
+// window is 784 bytes a column, 147 or 294 of them real, and all of it is fetched anew for every tap.  Here a pixel is four
+// channels (4 or 8 bytes), a tap row of up to eight pixels one or two MFMAs of reduction (32 bytes each), and a workgroup keeps the
+// input rows that its output pixels need, zero-padded, in LDS, with the weights of its 64 output channels beside them: everything
+// is fetched once, the fragments are plain LDS reads at a pixel's own address, no tap is masked, and the main loop has no
+// barrier.  The input is the caller's NCHW tensor (no layout pass) or a packed one.
+// What bounds it is the output, or for one image the start: weights and rows from beyond the L2, then 7 or 14 MFMAs.  So the weights
+// are fetched once per workgroup, which then walks over tiles of pixels, the next tile's on their way while this one's are
+// multiplied.  7x7, stride 2, 3 -> 64 channels, 224x224, whole calls, against the layout pass and the general kernel: fp16 batch 16
+// 29.2 -> 15.2 us (its 51 MB of output: 9.5), int8 requantised batch 8 18.4 -> 9.3, one image 8.6 -> 5.6; 4 -> 512 channels, 112x112,
+// batch 4, bf16, 45.7 -> 27.8.  A tile per workgroup, without the walk: 17.8, 9.2, 5.6 and 32.8.
+#include <cstring>
+
+#include "unit_internal.h"
+
+namespace unit {
+
+enum { NARROW_NCHW = 0, NARROW_PACKED = 1 };        // input: NCHW, or packed pixels of 16 bytes
+enum { NARROW_BM = 64, NARROW_SMEM = 96 * 1024 };
+
+template <int DT> struct NarrowPixel {
+    static constexpr int ES = (DT == DT_F16 || DT == DT_BF16) ? 2 : 1;
+    static constexpr int PXB = 4 * ES;              // bytes of a pixel in LDS
+};
+
+// Four pixels of one input row, as loaded: the words of each pixel (packed) or of each channel (NCHW).  row_at: index of the row's
+// first pixel (packed), or of its first element in channel 0.
+template <int ES, int SRC>
+__device__ __forceinline__ void load_pixels(const NarrowArgs &g, long row_at, int w0, unsigned (&c)[4][ES])
+{
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint8_t *src = SRC == NARROW_PACKED ? g.x + (row_at + w0 + k) * 16 : g.x + (row_at + (long)(k < g.C ? k : 0) * g.HW + w0) * ES;
+        __builtin_memcpy(c[k], src, 4 * ES);        // (any alignment)
+    }
+}
+// ... and the words px[e] of pixel e
+template <int ES, int SRC>
+__device__ __forceinline__ void to_pixels(const NarrowArgs &g, unsigned (&c)[4][ES], unsigned (&px)[4][ES])
+{
+    if constexpr (SRC == NARROW_PACKED) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int i = 0; i < ES; ++i) px[e][i] = c[e][i];
+    } else {
+#pragma unroll
+        for (int k = 1; k < 4; ++k)
+#pragma unroll
+            for (int i = 0; i < ES; ++i) c[k][i] = k < g.C ? c[k][i] : 0u;
+        if constexpr (ES == 1) {
+            const unsigned lo01 = __builtin_amdgcn_perm(c[1][0], c[0][0], 0x05010400u), hi01 = __builtin_amdgcn_perm(c[1][0], c[0][0], 0x07030602u);
+            const unsigned lo23 = __builtin_amdgcn_perm(c[3][0], c[2][0], 0x05010400u), hi23 = __builtin_amdgcn_perm(c[3][0], c[2][0], 0x07030602u);
+            px[0][0] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u);
+            px[1][0] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u);
+            px[2][0] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u);
+            px[3][0] = __builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    px[e][i] = __builtin_amdgcn_perm(c[2 * i + 1][e >> 1], c[2 * i][e >> 1], (e & 1) ? 0x07060302u : 0x05040100u);
+        }
+    }
+}
+
+// WGM x WGN waves; a wave has TM MFMA tiles of 32 channels and NG of 32 pixels.  JN: MFMAs of 32 bytes per tap row.
+template <int DT, int TM, int WGM, int WGN, int NG, int JN, int SRC, int EPI>
+__global__ void __launch_bounds__(WGM * WGN * 64, (DT == DT_F16 || DT == DT_BF16 || EPI == EPI_REQUANT) ? 2 : 3)
+narrow_kernel(const NarrowArgs g)
+{
+    typedef Mma<DT, 32> M;
+    typedef typename M::acc_t acc_t;
+    typedef typename M::elem_t elem_t;
+    typedef typename M::frag_t frag_t;
+    constexpr int FW = M::FW, ES = NarrowPixel<DT>::ES, PXB = NarrowPixel<DT>::PXB, NT = WGM * WGN * 64;
+    constexpr int BN = WGN * NG * 32, BM = WGM * TM * 32;
+    constexpr bool FLOATS = DT == DT_F16 || DT == DT_BF16 || DT == DT_FP8, UNSIGNED = DT == DT_U8B;
+    static_assert(BM == NARROW_BM && WGM * WGN == 4, "four waves on 64 channels");
+    static_assert(FW == 1 || JN == 1, "32-byte fragments take two tap rows");
+
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WGN, wn = wave % WGN, half = lane >> 5, lrow = lane & 31;
+    const int row0 = blockIdx.y * BM;
+    const int rows_here = g.K - row0 < BM ? g.K - row0 : BM;
+    uint8_t *win = smem + g.a_bytes;
+    // the tile being worked on, and the one whose pixels are being fetched
+    struct Tile { int n, col0, last, p0, nrows, h0; };                          // last: its last output pixel; input rows h0 .. h0 + nrows - 1
+    auto tile_at = [&](int t) {
+        Tile x;
+        x.n = divu(t, g.dv_tiles);
+        x.col0 = (t - x.n * (int)g.dv_tiles.d) * BN;
+        x.last = (x.col0 + BN < g.PQ ? x.col0 + BN : g.PQ) - 1;
+        x.p0 = divu(x.col0, g.dv_q);
+        x.nrows = (divu(x.last, g.dv_q) - x.p0) * g.sh + g.R;
+        x.h0 = x.p0 * g.sh - g.ph;
+        return x;
+    };
+    Tile at = tile_at(blockIdx.x);
+
+    // Weights of the tile, [channel][tap row][eight taps], from rows of 16-byte taps, and the rows of the window in pieces of four
+    // pixels: what a 7x7 window needs is requested before LDS is cleared (taps past the window and pixels outside the image
+    // stay zero), so that one trip to memory stands in front of the main loop.
+    constexpr int TAPS = 13, PIECES = 3;
+    const int taps = rows_here * (int)g.dv_rs.d;
+    const uint8_t *wsrc = g.w + (long)row0 * g.dv_rs.d * 16;
+    unsigned wt[TAPS][ES], raw[PIECES][4][ES];
+    auto load_weights = [&](int i0) {               // (no branches around the loads: what is past the end loads the last tap again)
+#pragma unroll
+        for (int t = 0; t < TAPS; ++t) {
+            const int i = i0 + t * NT + tid;
+            __builtin_memcpy(wt[t], wsrc + (unsigned)(i < taps ? i : taps - 1) * 16u, 4 * ES);
+        }
+    };
+    auto put_weights = [&](int i0) {
+#pragma unroll
+        for (int t = 0; t < TAPS; ++t) {
+            const int idx = i0 + t * NT + tid;
+            const int k = divu(idx, g.dv_rs), rs = idx - k * (int)g.dv_rs.d, r = divu(rs, g.dv_s), s = rs - r * (int)g.dv_s.d;
+            if (idx < taps)
+                __builtin_memcpy(__builtin_assume_aligned(smem + k * g.a_pitch + r * (JN * 32) + s * PXB, PXB), wt[t], PXB);
+        }
+    };
+    auto piece = [&](int i, int &row, int &w0) {    // window row and first pixel of piece i
+        row = divu(i, g.dv_chunk);
+        w0 = (i - row * (int)g.dv_chunk.d) * 4;
+        w0 = w0 + 4 <= g.W ? w0 : g.W - 4;          // (the last piece of a row repeats pixels)
+    };
+    auto load_window = [&](const Tile &x, int i0) {
+#pragma unroll
+        for (int t = 0; t < PIECES; ++t) {
+            int row, w0;
+            piece(i0 + t * NT + tid, row, w0);
+            int h = x.h0 + row;
+            h = h < 0 ? 0 : h < g.H ? h : g.H - 1;  // (rows outside the image are loaded from its edge and not used)
+            load_pixels<ES, SRC>(g, SRC == NARROW_PACKED ? ((long)x.n * g.H + h) * g.W : (long)x.n * g.C * g.HW + (long)h * g.W, w0, raw[t]);
+        }
+    };
+    auto put_window = [&](const Tile &x, int i0) {
+#pragma unroll
+        for (int t = 0; t < PIECES; ++t) {
+            const int i = i0 + t * NT + tid;
+            int row, w0;
+            piece(i, row, w0);
+            unsigned px[4][ES];
+            to_pixels<ES, SRC>(g, raw[t], px);
+            const bool in = (unsigned)(x.h0 + row) < (unsigned)g.H;             // (rows outside the image are zeros)
+            if (row < x.nrows) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+#pragma unroll
+                    for (int k = 0; k < ES; ++k) px[e][k] = (in ? px[e][k] : 0u) ^ (UNSIGNED ? 0x80808080u : 0u);
+                    __builtin_memcpy(__builtin_assume_aligned(win + row * g.win_pitch + (w0 + e + g.pw) * PXB, PXB), px[e], PXB);
+                }
+            }
+        }
+    };
+    load_weights(0);
+    load_window(at, 0);
+    for (int i = tid; i < g.clear; i += NT) {
+        const int z = UNSIGNED && i * 16 >= g.a_bytes ? (int)0x80808080 : 0;
+        reinterpret_cast<v4i *>(smem)[i] = v4i{z, z, z, z};
+    }
+    __syncthreads();
+    put_weights(0);
+    for (int i0 = TAPS * NT; i0 < taps; i0 += TAPS * NT) {
+        load_weights(i0);
+        put_weights(i0);
+    }
+    for (int t = blockIdx.x;;) {
+    put_window(at, 0);
+    for (int i0 = PIECES * NT; i0 < at.nrows * (int)g.dv_chunk.d; i0 += PIECES * NT) {
+        load_window(at, i0);
+        put_window(at, i0);
+    }
+    __syncthreads();
+    t += gridDim.x;
+    const int n = at.n, col0 = at.col0, last = at.last, p0 = at.p0;
+    if (t < g.tiles) {                              // (under the products of this tile)
+        at = tile_at(t);
+        load_window(at, 0);
+    }
+
+    // fragments: a lane's 16 bytes are four pixels (one-byte types) or two of a tap row; its 32 bytes (fp8) a whole tap row
+    const uint8_t *af[TM], *bf[NG];
+    int pix[NG];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) af[i] = smem + ((wm * TM + i) * 32 + lrow) * g.a_pitch + half * 16 * FW;
+#pragma unroll
+    for (int j = 0; j < NG; ++j) {
+        pix[j] = col0 + (wn * NG + j) * 32 + lrow;
+        const int m = pix[j] <= last ? pix[j] : last, p = divu(m, g.dv_q), q = m - p * (int)g.dv_q.d;
+        bf[j] = win + (p - p0) * g.sh * g.win_pitch + q * g.sw * PXB + (FW == 1 ? half * 16 : 0);
+    }
+    acc_t acc[TM][NG];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < NG; ++j)
+#pragma unroll
+            for (int e = 0; e < M::NACC; ++e) acc[i][j][e] = 0;
+    // taps past the window have zero weights; a pixel that is infinite must not meet them
+    unsigned live[4 * FW];
+#pragma unroll
+    for (int t = 0; t < 4 * FW; ++t) live[t] = ((JN - 1) * 32 + (FW == 1 ? half * 16 : 0) + 4 * t) / PXB < g.S ? ~0u : 0u;
+    const int steps = FW == 1 ? g.R : (g.R + 1) / 2;
+#pragma unroll 2
+    for (int r = 0; r < steps; ++r) {
+#pragma unroll
+        for (int jn = 0; jn < JN; ++jn) {
+            frag_t a[TM], b[NG];
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+                __builtin_memcpy(&a[i], __builtin_assume_aligned(af[i] + (r * JN + jn) * 32 * FW, 16), 16 * FW);
+            const int tr = FW == 1 ? r : (2 * r + half < g.R ? 2 * r + half : g.R - 1);
+            const bool in = FW == 1 || 2 * r + half < g.R;
+#pragma unroll
+            for (int j = 0; j < NG; ++j) {
+                unsigned v[4 * FW];
+                __builtin_memcpy(v, __builtin_assume_aligned(bf[j] + tr * g.win_pitch + jn * 32, PXB), 16 * FW);
+#pragma unroll
+                for (int t = 0; t < 4 * FW; ++t) {
+                    if (FLOATS && jn == JN - 1) v[t] &= in ? live[t] : 0u;
+                    b[j][t] = (int)v[t];
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < NG; ++j) M::run(acc[i][j], a[i], b[j]);
+        }
+    }
+
+    if constexpr (EPI != EPI_REQUANT) {
+        elem_t *base = reinterpret_cast<elem_t *>(g.out) + ((long)n * g.K + row0) * g.PQ;
+        const __amdgpu_buffer_rsrc_t rsO = make_rsrc(base, UNIT_OOB);
+        auto store = [&](auto aux_c) {
+            constexpr int AUX = decltype(aux_c)::value;
+#pragma unroll
+            for (int j = 0; j < NG; ++j)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int a4 = 0; a4 < 4; ++a4) {
+                        const int lr = (wm * TM + i) * 32 + 8 * a4 + 4 * half;
+                        const unsigned at = pix[j] <= last ? (unsigned)(lr * g.PQ + pix[j]) * 4u : UNIT_OOB;
+                        v4i fix = {0, 0, 0, 0};
+                        if (UNSIGNED) fix = buf_load16(make_rsrc(g.fix, (unsigned)g.K * 4u), (unsigned)(row0 + lr) * 4u);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            elem_t v = acc[i][j][4 * a4 + e];
+                            if (UNSIGNED) v += (elem_t)fix[e];
+                            __builtin_amdgcn_raw_buffer_store_b32(to_bits(v), rsO, lr + e < rows_here ? at : UNIT_OOB,
+                                                                  (unsigned)(e * g.PQ) * 4u, AUX);
+                        }
+                    }
+        };
+        if (g.stream) store(IntC<2>{});
+        else          store(IntC<0>{});
+    } else {
+        // int8 results wait in LDS, a block of NG x 32 pixels per wave, and leave as 16-byte pieces: of consecutive channels
+        // (packed) or of consecutive pixels (NCHW)
+        const __amdgpu_buffer_rsrc_t rsS = make_rsrc(g.scale, (unsigned)g.K * 4u);
+        const __amdgpu_buffer_rsrc_t rsBi = make_rsrc(g.bias, g.bias ? (unsigned)g.K * 4u : 0u);
+        constexpr int CH = TM * 32, PP = CH + 16, PC = 48;          // a pixel's and a channel's pitch (32 pixels a channel)
+        constexpr int BLOCK = 32 * PP > CH * PC ? 32 * PP : CH * PC;
+        unsigned four[NG][TM][4];
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int a4 = 0; a4 < 4; ++a4) {
+                const unsigned at = (unsigned)(row0 + (wm * TM + i) * 32 + 8 * a4 + 4 * half) * 4u;
+                const v4i s4 = buf_load16(rsS, at), b4 = buf_load16(rsBi, at);      // (rows past the last: a zero scale, zero bytes)
+#pragma unroll
+                for (int j = 0; j < NG; ++j) {
+                    unsigned r[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int se = s4[e], be = b4[e];
+                        r[e] = requant_low((int)((unsigned)(int)acc[i][j][4 * a4 + e] + (unsigned)be), __uint_as_float((unsigned)se), g.relu);
+                    }
+                    four[j][i][a4] = __builtin_amdgcn_perm(r[1], r[0], 0x0c0c0400u) | __builtin_amdgcn_perm(r[3], r[2], 0x04000c0cu);
+                }
+            }
+        uint8_t *mine = smem + g.clear * 16 + wave * BLOCK;
+        const int ch0 = row0 + wm * CH;             // first channel of the wave
+#pragma unroll
+        for (int j = 0; j < NG; ++j) {
+            const int m0 = col0 + (wn * NG + j) * 32;
+            if (g.out_packed) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int a4 = 0; a4 < 4; ++a4)
+                        *reinterpret_cast<unsigned *>(mine + lrow * PP + i * 32 + 8 * a4 + 4 * half) = four[j][i][a4];
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int it = 0; it < 32 * CH / 16 / 64; ++it) {
+                    const int px = (it * 64 + lane) / (CH / 16), cc = (it * 64 + lane) % (CH / 16) * 16;
+                    const v4i v = *reinterpret_cast<const v4i *>(mine + px * PP + cc);
+                    if (m0 + px <= last && ch0 + cc < g.packed_ld)
+                        *reinterpret_cast<v4i *>(g.out_packed + ((long)n * g.PQ + m0 + px) * g.packed_ld + ch0 + cc) = v;
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+            if (g.out_i8) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int a4 = 0; a4 < 4; ++a4)
+                        *reinterpret_cast<unsigned *>(mine + (i * 32 + 8 * a4 + 4 * half + (lane & 3)) * PC + (lrow & ~3)) =
+                            transpose_quad_bytes(four[j][i][a4], lane);
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int it = 0; it < TM; ++it) {
+                    const int ch = (it * 64 + lane) / 2, px = (lane & 1) * 16;
+                    const uint8_t *src = mine + ch * PC + px;
+                    int8_t *dst = g.out_i8 + ((long)n * g.K + ch0 + ch) * g.PQ + m0 + px;
+                    if (ch0 + ch < g.K) {
+                        if (m0 + px + 16 <= last + 1) {
+                            const v4i v = *reinterpret_cast<const v4i *>(src);
+                            __builtin_memcpy(dst, &v, 16);          // (any byte alignment)
+                        } else {
+                            for (int e = 0; m0 + px + e <= last; ++e) dst[e] = (int8_t)src[e];
+                        }
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
+    }
+    if (t >= g.tiles) return;
+    __syncthreads();                                // (every wave has read this tile's window)
+    }
+}
+
+// Bytes of LDS and the tile of a layer: 256 pixels per workgroup where those fill the chip, else 64 (the first layer above, fp16 batch 16,
+// 24.5 us on 64 pixels, 17.8 on 256; batch 6 11.9 / 8.8; one image, where 49 tiles of 256 are a fifth of the chip, takes 64).  128 pixels:
+// 18.5 us at batch 16.
+struct NarrowPlan { bool big; int smem; };
+
+static bool narrow_plan(int dtype, const NarrowShape &s, NarrowArgs *a, NarrowPlan *p)
+{
+    const bool wide = dtype == DT_F16 || dtype == DT_BF16;          // two-byte elements
+    if (s.C > 4 || s.S > 8 || s.W < 4) return false;
+    const int pxb = wide ? 8 : 4, jn = wide && s.S > 4 ? 2 : 1;
+    const int tap_rows = dtype == DT_FP8 ? (s.R + 1) / 2 * 2 : s.R;
+    const long a_pitch = (long)tap_rows * jn * 32 + 16;             // (16 bytes more: the rows of a fragment read fall on all banks)
+    const int taps = jn * 32 / pxb;                                 // pixels that a fragment row spans
+    long px = (long)(s.Q - 1) * s.sw + taps;
+    if (px < s.W + 2L * s.pw) px = s.W + 2L * s.pw;                 // (the window holds whole input rows)
+    const long win_pitch = (px * pxb + 15) / 16 * 16;
+    const long tiles = (long)(s.PQ + 255) / 256 * s.N * ((s.K + NARROW_BM - 1) / NARROW_BM);
+    auto smem = [&](int bn) {
+        long out_rows = (bn + s.Q - 2) / s.Q + 1;
+        if (out_rows > s.P) out_rows = s.P;
+        return NARROW_BM * a_pitch + ((out_rows - 1) * s.sh + s.R) * win_pitch;
+    };
+    constexpr int WAIT = 12 * 1024;                                 // (where the requantised results of four waves wait)
+    p->big = tiles >= 256 && smem(256) + WAIT <= NARROW_SMEM;
+    const long need = smem(p->big ? 256 : 64);
+    if (need + WAIT > NARROW_SMEM) return false;
+    a->clear = (int)(need / 16);
+    p->smem = (int)need + (a->out_i8 || a->out_packed ? WAIT : 0);
+    a->a_pitch = (int)a_pitch;  a->a_bytes = (int)(NARROW_BM * a_pitch);  a->win_pitch = (int)win_pitch;
+    return true;
+}
+
+bool narrow_fits(int dtype, const NarrowShape &s)
+{
+    NarrowArgs a;
+    std::memset(&a, 0, sizeof a);
+    NarrowPlan p;
+    return narrow_plan(dtype, s, &a, &p);
+}
+
+template <int DT, int TM, int WGM, int WGN, int NG, int JN, int SRC, int EPI>
+static hipError_t go(const NarrowArgs &a, int smem, dim3 grid, hipStream_t st)
+{
+    auto kern = narrow_kernel<DT, TM, WGM, WGN, NG, JN, SRC, EPI>;
+    static bool attr_set = false;                   // benign race: the call is idempotent
+    if (smem > 64 * 1024 && !attr_set) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, NARROW_SMEM);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    hipLaunchKernelGGL(kern, grid, dim3(256), smem, st, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_narrow(int dtype, const NarrowShape &s, bool packed, NarrowArgs a, hipStream_t st)
+{
+    NarrowPlan p;
+    if (!narrow_plan(dtype, s, &a, &p)) return hipErrorInvalidValue;
+    auto make = [](long d) { DivU v;  v.d = d > 1 ? (unsigned)d : 1u;  v.m = d > 1 ? (unsigned)((1ULL << 32) / (unsigned long long)d) : 0xffffffffu;  return v; };
+    a.C = s.C;  a.H = s.H;  a.W = s.W;  a.HW = s.H * s.W;  a.K = s.K;  a.R = s.R;  a.S = s.S;
+    a.PQ = s.PQ;  a.sh = s.sh;  a.sw = s.sw;  a.ph = s.ph;  a.pw = s.pw;
+    a.dv_q = make(s.Q);  a.dv_rs = make((long)s.R * s.S);  a.dv_s = make(s.S);  a.dv_chunk = make((s.W + 3) / 4);
+    a.stream = s.PQ % 16 == 0;
+    const int bn = p.big ? 256 : 64;
+    const int tiles_img = (s.PQ + bn - 1) / bn, row_tiles = (s.K + NARROW_BM - 1) / NARROW_BM;
+    if (row_tiles > 65535 || (long)tiles_img * s.N >= (1L << 24)) return hipErrorInvalidValue;
+    a.tiles = tiles_img * s.N;
+    a.dv_tiles = make(tiles_img);
+    // two workgroups per compute unit, which walk over the tiles: weights are fetched and laid out once, the next tile's pixels
+    // arrive while this one's are multiplied (as fast as three per unit, 15.2 us; four, which do not fit beside each other, 20.0)
+    const long rounds = ((long)a.tiles * row_tiles + 511) / 512;
+    const dim3 grid((unsigned)((a.tiles + rounds - 1) / rounds), row_tiles);
+    auto tile = [&](auto dt_c, auto jn_c, auto src_c, auto epi_c) {
+        constexpr int DT = decltype(dt_c)::value, JN = decltype(jn_c)::value, SRC = decltype(src_c)::value, EPI = decltype(epi_c)::value;
+        return p.big ? go<DT, 2, 1, 4, 2, JN, SRC, EPI>(a, p.smem, grid, st) : go<DT, 1, 2, 2, 1, JN, SRC, EPI>(a, p.smem, grid, st);
+    };
+    auto source = [&](auto dt_c, auto jn_c, auto epi_c) {
+        return packed ? tile(dt_c, jn_c, IntC<NARROW_PACKED>{}, epi_c) : tile(dt_c, jn_c, IntC<NARROW_NCHW>{}, epi_c);
+    };
+    auto width = [&](auto dt_c) {
+        return s.S > 4 ? source(dt_c, IntC<2>{}, IntC<EPI_RAW>{}) : source(dt_c, IntC<1>{}, IntC<EPI_RAW>{});
+    };
+    switch (dtype) {
+    case DT_I8:
+        return a.out_i8 || a.out_packed ? source(IntC<DT_I8>{}, IntC<1>{}, IntC<EPI_REQUANT>{}) : source(IntC<DT_I8>{}, IntC<1>{}, IntC<EPI_RAW>{});
+    case DT_U8B:  return source(IntC<DT_U8B>{}, IntC<1>{}, IntC<EPI_RAW>{});
+    case DT_FP8:  return source(IntC<DT_FP8>{}, IntC<1>{}, IntC<EPI_RAW>{});
+    case DT_F16:  return width(IntC<DT_F16>{});
+    case DT_BF16: return width(IntC<DT_BF16>{});
+    default:      return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace unit

@@ -72,6 +72,11 @@ inline bool byte_type(int dtype) { return dtype == UNIT_I8 || dtype == UNIT_U8I8
 inline int elem_size(int dtype) { return (byte_type(dtype) || dtype == UNIT_FP8) ? 1 : 2; }
 // what the layout kernels need to know: one- or two-byte elements
 inline int storage_dtype(int dtype) { return elem_size(dtype) == 1 ? DT_I8 : DT_F16; }
+// operand type of the conv kernels (unsigned activations are the column operand)
+inline int narrow_dtype(int dtype)
+{
+    return dtype == UNIT_I8 ? DT_I8 : dtype == UNIT_F16 ? DT_F16 : dtype == UNIT_BF16 ? DT_BF16 : dtype == UNIT_U8I8 ? DT_U8B : DT_FP8;
+}
 inline long max_reduction(int dtype)
 {
     return dtype == UNIT_I8 ? UNIT_MAX_REDUCTION_I8 : dtype == UNIT_U8I8 ? UNIT_MAX_REDUCTION_U8I8 : 0x7fffffffL;
@@ -282,6 +287,17 @@ bool nchw_shift_ok(const ConvND *d, int dtype, const ConvGeom &g, const void *x,
     return ((long)d->c * elem_size(dtype)) % t.bkb == 0;
 }
 
+// Convs that take kernels_narrow.hip: the first layer of a network (at most four input channels; its window and the image rows of a
+// tile must fit the LDS): faster than packing first and the general kernel at every size tried, 1.1 to 3 times (figures beside the
+// kernel).  Requantised results with a residual or raw sums beside them keep the general kernel, and so does a forced tile.
+bool narrow_ok(const ConvND *d, int dtype, const ConvGeom &g, const unit_requant *rq, const void *y_raw, NarrowShape *s)
+{
+    if (d->d != 1 || d->t != 1 || d->pad_d != 0 || d->c > 4 || tile_is_forced()) return false;
+    if (rq && (rq->residual || rq->residual_packed || y_raw)) return false;
+    *s = {d->n, d->c, d->h, d->w, d->k, d->r, d->s, g.p, g.q, g.p * g.q, d->stride_h, d->stride_w, d->pad_h, d->pad_w};
+    return (long)d->k <= 64L * 65535 && narrow_fits(narrow_dtype(dtype), *s);
+}
+
 // `xp` is the packed activation tensor, or (direct modes) the caller's NCHW tensor itself.
 int conv_packed(const ConvND *d, int dtype, const void *xp, const void *wp,
                 void *y_raw, const unit_requant *rq, int8_t *y_i8, void *y_packed,
@@ -293,7 +309,7 @@ int conv_packed(const ConvND *d, int dtype, const void *xp, const void *wp,
     int rc = conv_geom(d, dtype, &g);
     if (rc != UNIT_OK) return rc;
     if (!xp || !wp) return UNIT_EINVAL;
-    if (!aligned16(xp) || !aligned16(wp)) return UNIT_EINVAL;
+    if ((bsrc != BSRC_NARROW && !aligned16(xp)) || !aligned16(wp)) return UNIT_EINVAL;
     if (rq) {
         if (dtype != UNIT_I8 || !rq->scale || (!y_i8 && !y_packed)) return UNIT_EINVAL;
         if (rq->residual_packed && !aligned16(rq->residual_packed)) return UNIT_EINVAL;
@@ -303,6 +319,18 @@ int conv_packed(const ConvND *d, int dtype, const void *xp, const void *wp,
     if (ws && !aligned256(ws)) return UNIT_EINVAL;
     if (y_packed && !aligned16(y_packed)) return UNIT_EINVAL;     // written with 32-bit stores, read back as 16-byte chunks
     if ((dtype == UNIT_U8I8) != (fix != nullptr)) return UNIT_EINVAL;
+
+    NarrowShape ns;
+    if ((bsrc == BSRC_NARROW || bsrc == BSRC_GATHER) && narrow_ok(d, dtype, g, rq, rq ? y_raw : nullptr, &ns)) {
+        NarrowArgs na;
+        std::memset(&na, 0, sizeof na);
+        na.x = static_cast<const uint8_t *>(xp);  na.w = static_cast<const uint8_t *>(wp);
+        na.out = y_raw;  na.fix = fix;
+        if (rq) { na.scale = rq->scale;  na.bias = rq->bias;  na.relu = rq->relu ? 1 : 0; }
+        na.out_i8 = y_i8;  na.out_packed = static_cast<int8_t *>(y_packed);  na.packed_ld = pad_channels(d->k, UNIT_I8);
+        UNIT_HIP(launch_narrow(narrow_dtype(dtype), ns, bsrc == BSRC_GATHER, na, static_cast<hipStream_t>(stream)));
+        return UNIT_OK;
+    }
 
     IgemmArgs a;
     std::memset(&a, 0, sizeof a);
@@ -429,6 +457,11 @@ int conv_wpacked(const ConvND *d, int dtype, const void *x, const void *wp,
     split_b = conv_split_bytes(g, dtype, BSRC_GATHER);
     size_t act_b = packed_act_bytes_nd(d, dtype);
     if (!ws || ws_bytes < act_b + split_b) return UNIT_EWORKSPACE;
+    NarrowShape ns;
+    if (narrow_ok(d, dtype, g, rq, rq ? y_raw : nullptr, &ns)) {        // (the workspace stays untouched)
+        if (pw) UNIT_HIP(launch_pack(storage_dtype(dtype), pw, nullptr, static_cast<hipStream_t>(stream)));
+        return conv_packed(d, dtype, x, wp, y_raw, rq, y_i8, nullptr, nullptr, 0, stream, BSRC_NARROW, fix);
+    }
     uint8_t *xp = static_cast<uint8_t *>(ws);
     // A strided 1x1 conv reads one pixel in stride_h*stride_w: pack only those and run the
     // unit-stride 1x1 conv on the subsampled tensor (same reduction, same output).

@@ -62,6 +62,25 @@ hipError_t launch_unpack_act_i8(int n, int c, int h, int w, const void *xp, int8
 struct PadRows { const uint8_t *src; long ld_bytes; uint8_t *dst; long dst_ld; int rows; };
 hipError_t launch_pad_rows(const PadRows *ops, int nops, int row_bytes, int row_chunks, hipStream_t st);
 
+// Convs of at most four input channels (kernels_narrow.hip), on NCHW or packed activations and packed weights.  2-D, N images.
+struct NarrowShape { int N, C, H, W, K, R, S, P, Q, PQ, sh, sw, ph, pw; };
+struct NarrowArgs {
+    const uint8_t *x, *w;
+    void *out;                                                   // raw sums, or NULL
+    const float *scale;  const int32_t *bias;                    // requantised results: no residual
+    int8_t *out_i8, *out_packed;
+    const int32_t *fix;                                          // unsigned activations: 128 * (sum of each channel's weights)
+    int relu, packed_ld;
+    // (filled in by the launcher)
+    int C, H, W, HW, K, R, S, PQ, sh, sw, ph, pw, stream;
+    int a_pitch, a_bytes, win_pitch;                             // LDS: a channel's weights, all of them, a row of the window
+    int clear;                                                   // weights and window, in 16-byte pieces
+    int tiles;  DivU dv_tiles;                                   // tiles of pixels: in all, of an image
+    DivU dv_q, dv_rs, dv_s, dv_chunk;                            // Q, R * S, S, pieces of four pixels in a row of the image
+};
+bool narrow_fits(int dtype, const NarrowShape &s);               // dtype: DT_*, unsigned activations DT_U8B
+hipError_t launch_narrow(int dtype, const NarrowShape &s, bool packed, NarrowArgs a, hipStream_t st);
+
 // out[r] = 128 * sum of the signed bytes of row r (rows 16-byte aligned, chunks*16 bytes long)
 hipError_t launch_rowsum128_i8(const void *m, long ld, int rows, int chunks, int32_t *out, hipStream_t st);
 
