@@ -1,4 +1,4 @@
-"""Thin ctypes binding of libunit.so: argument marshalling only.
+"""Thin binding of libunit.so: argument marshalling only (ctypes; the launching calls through csrc/pycall.c).
 
 Every function has the name and argument order of its C entry point (include/unit.h)
 and takes torch tensors on the GPU (or raw integer device addresses) where the C
@@ -63,6 +63,7 @@ class UnitError(RuntimeError):
 
 
 _lib = None
+_entries = {}           # launching entry points as native functions (csrc/pycall.c): arguments -> status, or None for unusual ones
 
 EXPORTS = [
     "unit_version", "unit_status_str", "unit_last_hip_error", "unit_conv2d_out_dims",
@@ -149,6 +150,19 @@ def load():
     for name, (res, args) in sig.items():
         fn = getattr(L, name)
         fn.restype, fn.argtypes = res, args
+    try:
+        from . import _unitcall
+    except ImportError as e:
+        raise ImportError(f"the binding's extension module is missing (make -C paper_2101_08458_amd/csrc): {e}") from e
+    addr = lambda name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value
+    for name in sig:
+        kind = ("matmul" if name.startswith("unit_matmul_") and name != "unit_matmul_workspace" else
+                "conv_i8" if name in ("unit_conv2d_i8", "unit_conv2d_wpacked_i8") else
+                "packed_i8" if name == "unit_conv2d_packed_i8" else
+                "conv" if sig[name] in ((ctypes.c_int, [dp, vp, vp, vp, vp, sz, vp]), (ctypes.c_int, [d3, vp, vp, vp, vp, sz, vp])) else None)
+        if kind:
+            _entries[name] = _unitcall.entry(kind, addr(name), unit_conv3d_desc if sig[name][1][0] is d3 else unit_conv2d_desc,
+                                             unit_requant)
     _lib = L
     return L
 
@@ -165,6 +179,7 @@ def _p(t):
 
 
 _torch = None           # torch, once a call has needed its current stream
+_asks = []              # not empty once they do
 _raw_stream = None      # device index -> handle of torch's current stream there, where this torch has it
 
 
@@ -178,6 +193,10 @@ def _current_stream():
         _torch = torch
     if _raw_stream is None or not _torch.cuda.is_initialized():     # (the public call initialises, or refuses in a forked child)
         return _torch.cuda.current_stream().cuda_stream
+    if not _asks:
+        from . import _unitcall
+        _unitcall.streams(_torch._C._cuda_getDevice, _raw_stream)   # (from now on the native entry points ask for themselves)
+        _asks.append(True)
     return _raw_stream(_torch._C._cuda_getDevice())
 
 
@@ -198,6 +217,42 @@ def _ws(ws):
 def _check(status, where):
     if status != UNIT_OK:
         raise UnitError(status, where)
+
+
+# (an entry of _entries returns None where ctypes has to look at the arguments)
+
+def _call_matmul(name, m, n, k, A, lda, B, ldb, C, ldc, ws, stream):
+    if not _entries:
+        load()
+    rc = _entries[name](m, n, k, A, lda, B, ldb, C, ldc, ws, stream)
+    if rc is None:
+        wp, wb = _ws(ws)
+        rc = getattr(load(), name)(m, n, k, _p(A), lda, _p(B), ldb, _p(C), ldc, wp, wb, _stream(stream))
+    if rc:
+        _check(rc, name)
+
+
+def _call_conv(name, d, x, w, y, ws, stream):
+    if not _entries:
+        load()
+    rc = _entries[name](d, x, w, y, ws, stream)
+    if rc is None:
+        wp, wb = _ws(ws)
+        rc = getattr(load(), name)(ctypes.byref(d), _p(x), _p(w), _p(y), wp, wb, _stream(stream))
+    if rc:
+        _check(rc, name)
+
+
+def _call_conv_i8(name, d, x, w, y_i32, rq, y_i8, ws, stream):
+    if not _entries:
+        load()
+    rc = _entries[name](d, x, w, y_i32, rq, y_i8, ws, stream)
+    if rc is None:
+        wp, wb = _ws(ws)
+        rc = getattr(load(), name)(ctypes.byref(d), _p(x), _p(w), _p(y_i32), ctypes.byref(rq) if rq is not None else None, _p(y_i8),
+                                   wp, wb, _stream(stream))
+    if rc:
+        _check(rc, name)
 
 
 def conv_desc(n, c, h, w, k, r, s, stride=(1, 1), pad=(0, 0)):
@@ -267,28 +322,19 @@ def unit_select_matmul(m, n, k, dtype):
 
 
 def unit_conv2d_i8(d, x, w, y_i32, rq, y_i8, ws, stream=None):
-    wp, wb = _ws(ws)
-    _check(load().unit_conv2d_i8(ctypes.byref(d), _p(x), _p(w), _p(y_i32),
-                                 ctypes.byref(rq) if rq is not None else None, _p(y_i8),
-                                 wp, wb, _stream(stream)), "unit_conv2d_i8")
+    _call_conv_i8("unit_conv2d_i8", d, x, w, y_i32, rq, y_i8, ws, stream)
 
 
 def unit_conv2d_f16(d, x, w, y, ws, stream=None):
-    wp, wb = _ws(ws)
-    _check(load().unit_conv2d_f16(ctypes.byref(d), _p(x), _p(w), _p(y), wp, wb, _stream(stream)),
-           "unit_conv2d_f16")
+    _call_conv("unit_conv2d_f16", d, x, w, y, ws, stream)
 
 
 def unit_matmul_i8(m, n, k, A, lda, B, ldb, C, ldc, ws=None, stream=None):
-    wp, wb = _ws(ws)
-    _check(load().unit_matmul_i8(m, n, k, _p(A), lda, _p(B), ldb, _p(C), ldc, wp, wb, _stream(stream)),
-           "unit_matmul_i8")
+    _call_matmul("unit_matmul_i8", m, n, k, A, lda, B, ldb, C, ldc, ws, stream)
 
 
 def unit_matmul_f16(m, n, k, A, lda, B, ldb, C, ldc, ws=None, stream=None):
-    wp, wb = _ws(ws)
-    _check(load().unit_matmul_f16(m, n, k, _p(A), lda, _p(B), ldb, _p(C), ldc, wp, wb, _stream(stream)),
-           "unit_matmul_f16")
+    _call_matmul("unit_matmul_f16", m, n, k, A, lda, B, ldb, C, ldc, ws, stream)
 
 
 def unit_pack_act_i8(n, c, h, w, x, xp, stream=None):
@@ -316,17 +362,19 @@ def unit_unpack_act_i8(n, c, h, w, xp, x, stream=None):
 
 
 def unit_conv2d_packed_i8(d, xp, wp, y_i32, rq, y_i8, y_packed, ws=None, stream=None):
-    wsp, wsb = _ws(ws)
-    _check(load().unit_conv2d_packed_i8(ctypes.byref(d), _p(xp), _p(wp), _p(y_i32),
-                                        ctypes.byref(rq) if rq is not None else None,
-                                        _p(y_i8), _p(y_packed), wsp, wsb, _stream(stream)),
-           "unit_conv2d_packed_i8")
+    if not _entries:
+        load()
+    rc = _entries["unit_conv2d_packed_i8"](d, xp, wp, y_i32, rq, y_i8, y_packed, ws, stream)
+    if rc is None:
+        wsp, wsb = _ws(ws)
+        rc = load().unit_conv2d_packed_i8(ctypes.byref(d), _p(xp), _p(wp), _p(y_i32), ctypes.byref(rq) if rq is not None else None,
+                                          _p(y_i8), _p(y_packed), wsp, wsb, _stream(stream))
+    if rc:
+        _check(rc, "unit_conv2d_packed_i8")
 
 
 def unit_conv2d_packed_f16(d, xp, wp, y, ws=None, stream=None):
-    wsp, wsb = _ws(ws)
-    _check(load().unit_conv2d_packed_f16(ctypes.byref(d), _p(xp), _p(wp), _p(y), wsp, wsb, _stream(stream)),
-           "unit_conv2d_packed_f16")
+    _call_conv("unit_conv2d_packed_f16", d, xp, wp, y, ws, stream)
 
 
 def unit_conv2d_wpacked_workspace(d, dtype):
@@ -334,10 +382,7 @@ def unit_conv2d_wpacked_workspace(d, dtype):
 
 
 def unit_conv2d_wpacked_i8(d, x, wp, y_i32, rq, y_i8, ws=None, stream=None):
-    wsp, wsb = _ws(ws)
-    _check(load().unit_conv2d_wpacked_i8(ctypes.byref(d), _p(x), _p(wp), _p(y_i32),
-                                         ctypes.byref(rq) if rq is not None else None, _p(y_i8),
-                                         wsp, wsb, _stream(stream)), "unit_conv2d_wpacked_i8")
+    _call_conv_i8("unit_conv2d_wpacked_i8", d, x, wp, y_i32, rq, y_i8, ws, stream)
 
 
 def unit_conv2d_wpacked_i8_static(d, x, wp, y_i32, rq, y_i8, stream=None):
@@ -347,9 +392,7 @@ def unit_conv2d_wpacked_i8_static(d, x, wp, y_i32, rq, y_i8, stream=None):
 
 
 def unit_conv2d_wpacked_f16(d, x, wp, y, ws=None, stream=None):
-    wsp, wsb = _ws(ws)
-    _check(load().unit_conv2d_wpacked_f16(ctypes.byref(d), _p(x), _p(wp), _p(y), wsp, wsb, _stream(stream)),
-           "unit_conv2d_wpacked_f16")
+    _call_conv("unit_conv2d_wpacked_f16", d, x, wp, y, ws, stream)
 
 
 def conv3d_desc(n, c, d, h, w, k, t, r, s, stride=(1, 1, 1), pad=(0, 0, 0)):
@@ -368,13 +411,11 @@ def unit_conv3d_workspace(d, dtype):
 
 
 def unit_conv3d_i8(d, x, w, y, ws, stream=None):
-    wsp, wsb = _ws(ws)
-    _check(load().unit_conv3d_i8(ctypes.byref(d), _p(x), _p(w), _p(y), wsp, wsb, _stream(stream)), "unit_conv3d_i8")
+    _call_conv("unit_conv3d_i8", d, x, w, y, ws, stream)
 
 
 def unit_conv3d_f16(d, x, w, y, ws, stream=None):
-    wsp, wsb = _ws(ws)
-    _check(load().unit_conv3d_f16(ctypes.byref(d), _p(x), _p(w), _p(y), wsp, wsb, _stream(stream)), "unit_conv3d_f16")
+    _call_conv("unit_conv3d_f16", d, x, w, y, ws, stream)
 
 
 def unit_maxpool_packed_i8(n, c, h, w, window, stride, pad, xp, yp, stream=None):
@@ -417,38 +458,28 @@ def unit_debug_force_tile(tile, split_k):
 
 # ------------------------------------------------------------------ further operand types
 
-def _conv_simple(name, d, x, w, y, ws, stream):
-    wp, wb = _ws(ws)
-    _check(getattr(load(), name)(ctypes.byref(d), _p(x), _p(w), _p(y), wp, wb, _stream(stream)), name)
-
-
-def _matmul_simple(name, m, n, k, A, lda, B, ldb, C, ldc, ws, stream):
-    wp, wb = _ws(ws)
-    _check(getattr(load(), name)(m, n, k, _p(A), lda, _p(B), ldb, _p(C), ldc, wp, wb, _stream(stream)), name)
-
-
 def unit_conv2d_bf16(d, x, w, y, ws, stream=None):
-    _conv_simple("unit_conv2d_bf16", d, x, w, y, ws, stream)
+    _call_conv("unit_conv2d_bf16", d, x, w, y, ws, stream)
 
 
 def unit_conv2d_u8i8(d, x, w, y, ws, stream=None):
-    _conv_simple("unit_conv2d_u8i8", d, x, w, y, ws, stream)
+    _call_conv("unit_conv2d_u8i8", d, x, w, y, ws, stream)
 
 
 def unit_conv2d_fp8(d, x, w, y, ws, stream=None):
-    _conv_simple("unit_conv2d_fp8", d, x, w, y, ws, stream)
+    _call_conv("unit_conv2d_fp8", d, x, w, y, ws, stream)
 
 
 def unit_matmul_fp8(m, n, k, A, lda, B, ldb, C, ldc, ws=None, stream=None):
-    _matmul_simple("unit_matmul_fp8", m, n, k, A, lda, B, ldb, C, ldc, ws, stream)
+    _call_matmul("unit_matmul_fp8", m, n, k, A, lda, B, ldb, C, ldc, ws, stream)
 
 
 def unit_matmul_bf16(m, n, k, A, lda, B, ldb, C, ldc, ws=None, stream=None):
-    _matmul_simple("unit_matmul_bf16", m, n, k, A, lda, B, ldb, C, ldc, ws, stream)
+    _call_matmul("unit_matmul_bf16", m, n, k, A, lda, B, ldb, C, ldc, ws, stream)
 
 
 def unit_matmul_u8i8(m, n, k, A, lda, B, ldb, C, ldc, ws=None, stream=None):
-    _matmul_simple("unit_matmul_u8i8", m, n, k, A, lda, B, ldb, C, ldc, ws, stream)
+    _call_matmul("unit_matmul_u8i8", m, n, k, A, lda, B, ldb, C, ldc, ws, stream)
 
 
 # ------------------------------------------------------------------ applicability inspection (host only)
