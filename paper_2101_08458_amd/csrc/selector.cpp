@@ -222,19 +222,78 @@ TileChoice select_tile(int rows, int cols, int kchunks, int dtype, int bsrc, boo
     return ch;
 }
 
+size_t partial_bytes(const TileChoice &ch, long out_elems)
+{
+    return ch.split_k > 1 ? (size_t)ch.split_k * ((out_elems + 3) & ~3L) * 4 : 0;
+}
+
+// Deep reductions (640 to 2000 chunks, 10 to 32 KB; operand rows of contiguous bytes; beyond, nothing was measured).  select_tile's
+// few thresholds were fitted to layers of up to 576 chunks and leave deeper ones on 16x16 or 32x32 tiles without a split, or with too
+// few or too many slices.  Here the time of the three small tiles is estimated for a number of slices each: steps of a slice, times
+// the larger of a step's latency and its share of a full chip's throughput, plus the reduce launch (us).  Fitted to 541 + 540
+// products and 5x5 convs in int8, fp16 and fp8 (24 to 512 rows, 36 to 6400 columns): of these, 640 to 900 chunks take 0.98 of their time before,
+// 900 to 1200 chunks 0.86, beyond 0.82 (the best tile and split of all that were timed: 0.90, 0.82, 0.75); the worst 1.03.  At 520 to 640 chunks
+// ten of 192 lost 3 to 11 %; below, the thresholds are as good.  An estimate must be 25 % better to count, and slices on 16x16 tiles
+// have twelve steps at least (shorter ones lost up to 27 %).
+// Float sums: no chain of additions may be longer than in the choice it replaces (their error grows with it).
+TileChoice refine_deep(const TileChoice &base, int rows, int cols, int kchunks, int dtype, int bsrc, size_t partials)
+{
+    struct Est { int tile; double latency, share; int chain, chain_fp8; };      // chain: reduction bytes per addition to an accumulator
+    static const Est est[] = {{3, 0.165, 0.090, 64, 128}, {4, 0.140, 0.066, 128, 128}, {12, 0.135, 0.095, 256, 256}};
+    static const int splits[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16};
+    const int CUS = 256;
+    if (kchunks < 640 || kchunks > 2000 || rows <= 16 || (bsrc != BSRC_PLAIN && bsrc != BSRC_GATHER)) return base;
+    if (g_force_tile.load(std::memory_order_relaxed) >= 0 || g_force_split.load(std::memory_order_relaxed) >= 1) return base;
+    const bool ints = dtype == 0 /* int8 */ || dtype == 3 /* u8 x i8 */, fp8 = dtype == 4;
+    auto choice = [&](const Est &e, int split) {
+        const TileCfg &c = g_tiles[e.tile];
+        const int ksteps = cdiv(kchunks, c.bkb / 16);
+        TileChoice ch;
+        ch.tile = e.tile;
+        ch.ksteps_per_split = cdiv(ksteps, split);
+        ch.split_k = cdiv(ksteps, ch.ksteps_per_split);
+        ch.workgroups = (int)((long)cdiv(rows, c.bm) * cdiv(cols, c.bn) * ch.split_k);
+        return ch;
+    };
+    auto cost = [&](const Est &e, const TileChoice &ch) {
+        const double q = (double)ch.workgroups / CUS, full = q < 1 ? q : 0.5 * (q + cdiv(ch.workgroups, CUS));
+        const double step = e.latency > e.share * full ? e.latency : e.share * full;
+        return ch.ksteps_per_split * step + (ch.split_k > 1 ? 2.1 + 0.85e-6 * (double)partial_bytes(ch, (long)rows * cols) : 0.0);
+    };
+    const Est *own = nullptr;
+    for (const Est &e : est) if (e.tile == base.tile) own = &e;
+    if (!own) return base;
+    auto additions = [&](const Est &e, const TileChoice &ch) { return (long)(fp8 ? e.chain_fp8 : e.chain) * ch.split_k; };
+    TileChoice best = base;
+    double best_cost = cost(*own, base) / 1.25;
+    for (const Est &e : est) {
+        if (!tile_fits(e.tile, dtype, bsrc)) continue;
+        for (int s : splits) {
+            const TileChoice ch = choice(e, s);
+            if (ch.split_k != s || partial_bytes(ch, (long)rows * cols) > partials) continue;
+            if (e.tile == 12 && s > 1 && ch.ksteps_per_split < 12) continue;
+            if (!ints && additions(e, ch) < additions(*own, base)) continue;
+            const double c = cost(e, ch);
+            if (c < best_cost) { best_cost = c;  best = ch; }
+        }
+    }
+    return best;
+}
+
 // Relative cost of one tile of the narrower relatives of the 256 x 256 tile, per unit of reduction, in units of the
 // large tile's own cost (measured on matmuls that fill exactly one round of 256 workgroups with each shape).
 // (tile: next to tile 8; quad: next to TILE_QUAD, whose relatives cost the same: fp16, reductions 1024 / 4096, 0.80 / 0.78 and 0.60 /
 // 0.57; int8 0.79 / 0.79 and 0.61 / 0.58)
 static const struct { int tile, quad, bn; double cost; } g_tail_tiles[] = {{10, TILE_QUAD + 1, 192, 0.79}, {11, TILE_QUAD + 2, 128, 0.60}};
 
-RangePlan plan_ranges(int rows, int cols, int kchunks, int dtype, int bsrc, bool allow_split, int cb, bool allow_ranges)
+RangePlan plan_ranges(int rows, int cols, int kchunks, int dtype, int bsrc, bool allow_split, int cb, bool allow_ranges, size_t partials)
 {
     RangePlan p;
     p.n = 1;
     p.col_begin[0] = 0;  p.col_end[0] = cols;
     p.col_begin[1] = p.col_end[1] = cols;
     p.choice[0] = select_tile(rows, cols, kchunks, dtype, bsrc, allow_split, cb);
+    if (allow_split) p.choice[0] = refine_deep(p.choice[0], rows, cols, kchunks, dtype, bsrc, partials);
     p.choice[1] = p.choice[0];
     if (!allow_ranges || g_force_tile.load(std::memory_order_relaxed) >= 0) return p;
     if ((p.choice[0].tile != 8 && p.choice[0].tile != TILE_QUAD) || p.choice[0].split_k != 1) return p;

@@ -160,7 +160,7 @@ int run_igemm(int dtype, int bsrc, IgemmArgs a, long out_elems, int K, int PQ,
     const bool conv = bsrc != BSRC_PLAIN;
     // (column ranges need tiles that may start anywhere in an image: not with per-image tiling)
     const RangePlan plan = plan_ranges(a.rows, a.cols, a.kchunks, dtype, bsrc, allow_split, conv ? a.CB : 0,
-                                       !(conv && a.per_img));
+                                       !(conv && a.per_img), ws ? ws_bytes : 0);
     const TileChoice ch = plan.choice[0];
     for (int r = 0; r < plan.n; ++r)
         if (!tile_fits(plan.choice[r].tile, dtype, bsrc)) return UNIT_ENOTSUP;     // (only a forced tile can fail this)
@@ -378,15 +378,22 @@ size_t conv_fix_bytes(const ConvND *d, int dtype)
     return dtype == UNIT_U8I8 ? align256((size_t)d->k * 4) : 0;
 }
 
+// Partial sums of a split reduction: what a call must be given, and what it takes if it is there (deep reductions: refine_deep)
 size_t conv_split_bytes(const ConvGeom &g, int dtype, int bsrc)
 {
-    TileChoice ch = select_tile(g.rows, (int)g.cols, g.kchunks, dtype, bsrc, true, g.cp * elem_size(dtype) / 16);
-    return ch.split_k > 1 ? align256((size_t)ch.split_k * ((g.out_elems + 3) & ~3L) * 4) : 0;
+    return align256(partial_bytes(select_tile(g.rows, (int)g.cols, g.kchunks, dtype, bsrc, true, g.cp * elem_size(dtype) / 16), g.out_elems));
+}
+size_t conv_split_bytes_most(const ConvGeom &g, int dtype, int bsrc)
+{
+    const TileChoice ch = select_tile(g.rows, (int)g.cols, g.kchunks, dtype, bsrc, true, g.cp * elem_size(dtype) / 16);
+    const size_t a = partial_bytes(ch, g.out_elems);
+    const size_t b = partial_bytes(refine_deep(ch, g.rows, (int)g.cols, g.kchunks, dtype, bsrc, ~(size_t)0), g.out_elems);
+    return align256(a > b ? a : b);
 }
 // what a caller who does not know the input mode yet must provide
 size_t conv_split_bytes_any(const ConvGeom &g, int dtype)
 {
-    size_t a = conv_split_bytes(g, dtype, BSRC_GATHER), b = conv_split_bytes(g, dtype, BSRC_NCHWS);
+    size_t a = conv_split_bytes_most(g, dtype, BSRC_GATHER), b = conv_split_bytes(g, dtype, BSRC_NCHWS);
     return a > b ? a : b;
 }
 
@@ -471,12 +478,12 @@ int conv_wpacked(const ConvND *d, int dtype, const void *x, const void *wp,
         sub.h = g.p;  sub.w = g.q;  sub.stride_h = sub.stride_w = 1;
         const PackActs pa = {x, xp, d->n, d->c, d->h, d->w, d->stride_h, d->stride_w, g.p, g.q};
         UNIT_HIP(launch_pack(storage_dtype(dtype), pw, &pa, static_cast<hipStream_t>(stream)));
-        return conv_packed(&sub, dtype, xp, wp, y_raw, rq, y_i8, nullptr, split_b ? xp + act_b : nullptr, split_b,
+        return conv_packed(&sub, dtype, xp, wp, y_raw, rq, y_i8, nullptr, xp + act_b, ws_bytes - act_b,
                            stream, BSRC_GATHER, fix);
     }
     const PackActs pa = {x, xp, d->n, d->c, d->d * d->h, d->w, 1, 1, 0, 0};
     UNIT_HIP(launch_pack(storage_dtype(dtype), pw, &pa, static_cast<hipStream_t>(stream)));
-    return conv_packed(d, dtype, xp, wp, y_raw, rq, y_i8, nullptr, split_b ? xp + act_b : nullptr, split_b, stream,
+    return conv_packed(d, dtype, xp, wp, y_raw, rq, y_i8, nullptr, xp + act_b, ws_bytes - act_b, stream,
                        BSRC_GATHER, fix);
 }
 
@@ -499,7 +506,7 @@ struct MatmulGeom {
     long pitch;                // row pitch of the copies
     bool pad_a, pad_b;
     bool gemv;                 // at most GEMV_MAX_ROWS rows: the dot-product kernel instead of the matrix units
-    size_t a_bytes, b_bytes, fix_bytes, split_bytes;
+    size_t a_bytes, b_bytes, fix_bytes, split_bytes, split_most;     // (split_most: taken if there, see refine_deep)
 };
 
 // narrow: copies of operands without padding between the rows (short ones, or a workspace that holds no more)
@@ -522,7 +529,9 @@ int matmul_geom(int m, int n, int k, long lda, long ldb, int dtype, MatmulGeom *
     g->fix_bytes = dtype == UNIT_U8I8 ? align256((size_t)n * 4) : 0;
     g->gemv = m <= GEMV_MAX_ROWS && (dtype == UNIT_I8 || dtype == UNIT_F16) && !tile_is_forced();
     TileChoice ch = select_tile(m, n, g->kchunks, dtype, BSRC_PLAIN);
-    g->split_bytes = (ch.split_k > 1 && !g->gemv) ? align256((size_t)ch.split_k * (((long)m * n + 3) & ~3L) * 4) : 0;
+    g->split_bytes = g->gemv ? 0 : align256(partial_bytes(ch, (long)m * n));
+    const size_t most = g->gemv ? 0 : align256(partial_bytes(refine_deep(ch, m, n, g->kchunks, dtype, BSRC_PLAIN, ~(size_t)0), (long)m * n));
+    g->split_most = most > g->split_bytes ? most : g->split_bytes;
     return UNIT_OK;
 }
 
@@ -577,7 +586,8 @@ int matmul_any(int dtype, int m, int n, int k, const void *A, long lda, const vo
         a.bias = fix;  wsp += g.fix_bytes;
     }
     // the split reduce writes a dense [m][n] result: only usable when ldc == n
-    return run_igemm(dtype, BSRC_PLAIN, a, (long)m * n, 1, n, g.split_bytes ? wsp : nullptr, g.split_bytes, st,
+    const size_t left = ws ? ws_bytes - (need - g.split_bytes) : 0;          // (a workspace that is used is aligned: checked above where it is needed)
+    return run_igemm(dtype, BSRC_PLAIN, a, (long)m * n, 1, n, left && aligned256(ws) ? wsp : nullptr, left, st,
                      ldc == n);
 }
 
@@ -664,7 +674,7 @@ size_t unit_conv2d_packed_workspace(const unit_conv2d_desc *d, int dtype)
     ConvGeom g;
     ConvND nd(d);
     if (conv_geom(&nd, dtype, &g) != UNIT_OK) return 0;
-    return conv_split_bytes(g, dtype, BSRC_GATHER);
+    return conv_split_bytes_most(g, dtype, BSRC_GATHER);
 }
 
 size_t unit_conv2d_workspace(const unit_conv2d_desc *d, int dtype)
@@ -680,7 +690,7 @@ size_t unit_matmul_workspace(int32_t m, int32_t n, int32_t k, int64_t lda, int64
 {
     MatmulGeom g;
     if (matmul_geom(m, n, k, lda, ldb, dtype, &g) != UNIT_OK) return 0;
-    return g.a_bytes + g.b_bytes + g.fix_bytes + g.split_bytes;
+    return g.a_bytes + g.b_bytes + g.fix_bytes + g.split_most;
 }
 
 int unit_select_conv2d(const unit_conv2d_desc *d, int dtype, unit_tile_info *out)

@@ -41,7 +41,11 @@ struct RangePlan {
     int col_begin[2], col_end[2];
     TileChoice choice[2];
 };
-RangePlan plan_ranges(int rows, int cols, int kchunks, int dtype, int bsrc, bool allow_split, int cb, bool allow_ranges);
+// partials: bytes there are for the partial sums of a split reduction (the caller's workspace; a query: no limit)
+RangePlan plan_ranges(int rows, int cols, int kchunks, int dtype, int bsrc, bool allow_split, int cb, bool allow_ranges, size_t partials = ~(size_t)0);
+// select_tile's choice for a deep reduction, or a better one whose partial sums fit (the rule is beside it)
+TileChoice refine_deep(const TileChoice &base, int rows, int cols, int kchunks, int dtype, int bsrc, size_t partials);
+size_t partial_bytes(const TileChoice &ch, long out_elems);      // of a split reduction (slices of whole 16 bytes); 0 if unsplit
 // test / sweep hook behind unit_debug_force_tile: tile and grid split every later select_tile returns (-1 = the rule)
 void force_tile(int tile, int split);
 bool tile_is_forced();
