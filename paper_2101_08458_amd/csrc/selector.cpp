@@ -300,6 +300,60 @@ RangePlan plan_ranges(int rows, int cols, int kchunks, int dtype, int bsrc, bool
     const int CUS = 256, BN = 256;
     const long tm = cdiv(rows, 256), tn = cdiv(cols, BN), nt = tm * tn;
     if (nt <= CUS || nt % CUS == 0) return p;
+    const bool quad = p.choice[0].tile == TILE_QUAD;
+    // Products of several rounds: one launch of a narrower tile, or of the large one, where it is estimated at 3 % less than two ranges.
+    // A round of large tiles takes about 13 us and 9 us per KiB of reduction, one of 192 columns 0.89 of it, of 128 columns 0.62 on four
+    // waves and 0.72 on eight, a partly filled one hardly less; as a second launch those of the ranges cost 0.87 (0.68) and a launch.
+    // Against two ranges alone: int8 4800x6784x896 65.7 -> 55.6 us, 6016x6080x3072 117 -> 108, fp16 4800x7552x3072 200 -> 189, 6336x3456x1536 74.4 -> 70.2,
+    // bf16 5183x3369x2048 83.9 -> 77.1, fp8 3200x4928x1536 43.3 -> 36.2, fp8 4160x4544x896 35.2 -> 31.2, the large tile alone in int8 6720x6336x512 60.2 -> 56.0
+    // (not in the types without four-wave tiles: fp8 6592x3712x896 40.3 us in two ranges, 44.7); of 60 products 19 changed, none of them lost.  Narrower tiles whose last round is at least half full: others were
+    // not among those that gained.  u8 x i8 is left out: 3102x5580x4096 107 -> 96 us, but 6577x3155x1024 45.0 -> 49.3.  Convs, whose tiles gather, gain from
+    // the second range: not here.
+    auto whole = [&](double tiles, double cost) {
+        const double r = tiles / CUS, up = (double)cdiv((long)tiles, CUS);
+        return cost * (up - 0.1 * (up - r));
+    };
+    const double second = 0.06 + 4.0 / (13.0 + 9.0 / 64 * kchunks);
+    auto one_launch = [&](double plan_cost) {       // the best single launch, if it beats the plan
+        const struct { int tile8, quad, bn; double cost; } one[] = {{8, TILE_QUAD, 256, 1.0}, {10, TILE_QUAD + 1, 192, 0.89}, {11, TILE_QUAD + 2, 128, tile_fits(TILE_QUAD, dtype, bsrc) ? 0.62 : 0.72}};
+        int best = -1;
+        double best_cost = 0.97 * plan_cost;
+        for (int i = tile_fits(TILE_QUAD, dtype, bsrc) ? 0 : 1; i < 3; ++i) {
+            const long tiles = tm * cdiv(cols, one[i].bn);
+            if (i > 0 && (tiles - 1) % CUS + 1 < CUS / 2) continue;
+            const double c = whole((double)tiles, one[i].cost);
+            if (c < best_cost) { best_cost = c;  best = i; }
+        }
+        if (best < 0) return false;
+        // (the narrower tiles on four waves also for short reductions: 15 against 10, int8 4800x6784x896 50.8 / 55.2 us, 2880x7808x512 equal)
+        const int t4 = one[best].quad, tile = best == 0 ? p.choice[0].tile : tile_fits(t4, dtype, bsrc) ? t4 : one[best].tile8;
+        if (!tile_fits(tile, dtype, bsrc)) return false;
+        const TileCfg &c = g_tiles[tile];
+        p.n = 1;
+        p.col_end[0] = cols;
+        p.choice[0].tile = tile;
+        p.choice[0].ksteps_per_split = cdiv(kchunks, c.bkb / 16);
+        p.choice[0].workgroups = (int)(tm * cdiv(cols, c.bn));
+        p.choice[1] = p.choice[0];
+        return true;
+    };
+    if (bsrc == BSRC_PLAIN && dtype != 3 /* u8 x i8 */) {
+        // what the ranges below would cost
+        const long m1 = (nt / CUS) * CUS / tm;
+        double plan = whole((double)nt, 1.0);
+        if (m1 > 0 && m1 < tn) {
+            const long rest = cols - m1 * BN;
+            const double large = (double)cdiv(tm * cdiv(rest, BN), CUS);
+            double tail = 0.92 * large;
+            for (unsigned i = 0; i < sizeof g_tail_tiles / sizeof g_tail_tiles[0]; ++i)
+                if (tm * cdiv(rest, g_tail_tiles[i].bn) <= CUS && g_tail_tiles[i].cost < tail &&
+                    tile_fits(quad ? g_tail_tiles[i].quad : g_tail_tiles[i].tile, dtype, bsrc)) {
+                    tail = g_tail_tiles[i].cost;
+                    plan = (double)cdiv(m1 * tm, CUS) + (g_tail_tiles[i].bn == 192 ? 0.87 : 0.68) + second;
+                }
+        }
+        if (one_launch(plan)) return p;
+    }
     // main range: the column tiles that make whole rounds of workgroups; tail: the rest
     const long n1 = (nt / CUS) * CUS / tm;
     if (n1 <= 0 || n1 >= tn) return p;
